@@ -19,19 +19,27 @@ struct AdjArgs {
     int32_t Sp;            // S rounded up to a multiple of 8
     int32_t v_per;         // antennas per y-block
     int32_t nvs;           // y-blocks
-    int32_t ppl;           // paths per lane of the kernel that runs this request
+    int32_t tile;          // paths per work item of the kernel that runs this request
     float fcf, sl_fs, tc;  // fc, slope / fs, chirp period
     float *tau_bar;        // [V][cap]
     float2 *abar_part;     // [nvs][cap]
     float *tdb_part;       // [nvs][cap] dL/d taudot partials
-    const float4 *nu_rows; // [V][C][2S + 8] non-uniform FFT rows (NULL: direct form)
-    float *nu_corr;        // [S] its 1/Psi table
+    const float4 *nu_rows; // non-uniform FFT rows of 2S + 8 points (NULL: direct form):
+                           // [V][C] of the chirp-row form, [V][q] of the node form
+    float *nu_corr;        // [S] 1/Psi table of the chirp-row form
+    float2 *td_rows;       // [V][q][2S + 8] node form: rows of the taudot sums
+    double *acc;           // sums over rays to clear (NULL: none)
+    int32_t n_acc;
+    NodePlan nd;           // nd.q = 0: not the node form
 };
 
 constexpr int kAdjRowsMax = 8;   // G rows staged in LDS at a time
 constexpr int kAdjPPL = 2;       // paths per lane, direct form
 constexpr int kNuPPL = 4;        // paths per lane, non-uniform FFT form
-constexpr int kAdjQueueDirect = 32;   // work counter of the direct form (queue[0]: the other)
+constexpr int kAdjQueueDirect = 32;   // work counters: of the direct form, of the chirp-row
+constexpr int kAdjQueueNode = 48;     // form (queue[0]) and of the node form
+constexpr int kNodeThreads = 512;     // threads of a node-form block
+constexpr int kNodePPL = 2;           // its paths per lane
 
 // ---- Eqs. 11-12 by a type-2 non-uniform FFT -------------------------------
 // For each (v, c) the two sums of the adjoint are finite Fourier series of one
@@ -294,6 +302,303 @@ __device__ __forceinline__ void adj_item_nu(const AdjArgs &a, float4 *rsh, const
         }
 }
 
+// ---- the node form of the adjoint (type-2 transform over Doppler nodes) -----
+// The kernel is one tap wider than the synthesis' (aliasing 9e-8 instead of
+// 8e-7 of the terms' RMS): the gradients of the pose, the medium and the
+// materials sum over all paths with cancellation and show that error.
+// Against 64 bits they come out 0.4 times as far off as with the chirp rows
+// (geometric mean over 40 scenes of 320^2 rays).
+// The transpose of the synthesis' node form (NodePlan, sbr_internal.h): per
+// (v, j) one row of the node sums
+//   H_j[s] = sum_c conj(G[v][c][s]) e^{2 pi j (c - cbar)(1 + s kappa) nu_j}
+// is transformed like a gradient row of the chirp-row form, and a path reads
+// kNu8W taps of q rows instead of one row per chirp; its chirp-weighted sum (the
+// taudot adjoint, Q with the weight c t_chirp) has rows of its own, made and
+// read only where a gradient that depends on it is asked for.
+
+// Node row (v, j) = blockIdx.x: the chirps summed against the node's phase
+// (thread groups take every groups-th chirp), weighted and deconvolved, then
+// the DFT as in k_nu_rows with the taudot sequence beside.  All of it in FP64:
+// a path reads a few node rows where it read one row per chirp, so rounding in
+// a row no longer averages over the chirps, and there are only V q rows (84 at
+// 12 antennas and 7 nodes: the launch is bound by its longest chain).
+constexpr int kNodeRowThreads = 512;
+struct D4 {
+    double x, y, z, w;
+};
+
+template <bool TD>
+__global__ __launch_bounds__(kNodeRowThreads) void k_node_adj_rows(const AdjArgs *__restrict__ args,
+                                                                   const int32_t *__restrict__ first, int m) {
+    extern __shared__ double nsd[];
+    __shared__ double kn[kNu8Taps];
+    int j = 0, hi = m;
+    while (hi - j > 1) {
+        const int mid = (j + hi) >> 1;
+        if (first[mid] <= (int)blockIdx.x) j = mid;
+        else hi = mid;
+    }
+    const AdjArgs &a = args[j];
+    const int S = a.S, M = 2 * S, RL = nu_row_len(S), Q = a.nd.q, C = a.C;
+    D4 *seq = reinterpret_cast<D4 *>(nsd);                    // [M] (P, Q) sequence
+    double2 *tw = reinterpret_cast<double2 *>(seq + M);       // [M]
+    double2 *sq2 = tw + M;                                    // [M] taudot sequence (TD)
+    D4 *part = reinterpret_cast<D4 *>(TD ? sq2 + M : sq2);    // [groups][cols], one per thread
+    const int row = (int)blockIdx.x - first[j], v = row / Q, k = row - v * Q;
+    const bool pow2 = (M & (M - 1)) == 0;
+    const int lg = 31 - __clz(M);
+    const double nu = a.nd.nu0 + a.nd.h * cospi((2.0 * k + 1.0) / (2.0 * Q));
+    if (threadIdx.x < kNu8Taps) kn[threadIdx.x] = nu8_kernel_sample((int)threadIdx.x);
+    for (int i = threadIdx.x; i < M; i += kNodeRowThreads) {
+        double sn, cs;
+        sincospi(2.0 * i / M, &sn, &cs);
+        tw[i] = make_double2(cs, sn);
+    }
+    __syncthreads();
+    // chirp sums of column s by the groups' threads, partial sums through LDS
+    const int cols = min(S, kNodeRowThreads), groups = kNodeRowThreads / cols;
+    const int g = (int)threadIdx.x / cols, col = (int)threadIdx.x % cols;
+    const auto G = gmem(a.G) + (size_t)v * C * S;
+    for (int s0 = 0; s0 < S; s0 += cols) {
+        const int s = s0 + col;
+        double pr = 0.0, pi = 0.0, tr = 0.0, ti = 0.0;
+        if (g < groups && s < S) {
+            const double rate = (1.0 + s * a.nd.kappa) * nu;
+#pragma unroll 4
+            for (int c = g; c < C; c += groups) {
+                const F2 x = G[(size_t)c * S + s];
+                const double ph = (double)(c - a.nd.cbar) * rate;
+                float sn, cs;
+                sincospif(2.0f * (float)(ph - rint(ph)), &sn, &cs);
+                const float zr = fmaf(x.x, cs, x.y * sn), zi = fmaf(x.x, sn, -x.y * cs);   // conj(G) e^{...}
+                pr += zr;
+                pi += zi;
+                if (TD) {
+                    tr += (double)c * zr;
+                    ti += (double)c * zi;
+                }
+            }
+        }
+        if (groups > 1) {
+            if (g < groups) part[g * cols + col] = D4{pr, pi, tr, ti};
+            __syncthreads();
+            if (g == 0) {
+                for (int q = 1; q < groups; q++) {
+                    const D4 x = part[q * cols + col];
+                    pr += x.x;
+                    pi += x.y;
+                    tr += x.z;
+                    ti += x.w;
+                }
+            }
+        }
+        if (g == 0 && s < S) {
+            const double r = nu8_corr_value(S, s, kn);
+            const double w2 = (double)a.sl_fs * s + (double)a.fcf;
+            const double hr = pr * r, hi2 = pi * r;
+            const int n = pow2 ? (s - S / 2) & (M - 1) : s;                      // mode s - S/2
+            const int pos = pow2 ? (int)(__brev((uint32_t)n) >> (32 - lg)) : s;
+            seq[pos] = D4{hr, hi2, hr * w2, hi2 * w2};
+            if (TD) sq2[pos] = make_double2(tr * (r * w2 * a.tc), ti * (r * w2 * a.tc));
+        }
+    }
+    if (pow2) {
+        // the other S modes are zero
+        for (int i = threadIdx.x; i < S; i += kNodeRowThreads) {
+            const int n = (i + S - S / 2) & (M - 1);
+            const int pos = (int)(__brev((uint32_t)n) >> (32 - lg));
+            seq[pos] = D4{0.0, 0.0, 0.0, 0.0};
+            if (TD) sq2[pos] = make_double2(0.0, 0.0);
+        }
+    }
+    __syncthreads();
+    float4 *out = const_cast<float4 *>(a.nu_rows) + (size_t)row * RL;
+    float2 *out2 = a.td_rows + (size_t)row * RL;
+    if (pow2) {
+        for (int half = 1; half < M; half <<= 1) {
+            const int tstep = M / (2 * half);
+            for (int i = threadIdx.x; i < M / 2; i += kNodeRowThreads) {
+                const int pos = i & (half - 1), j0 = ((i - pos) << 1) + pos, j1 = j0 + half;
+                const double2 w = tw[pos * tstep];
+                const D4 u = seq[j0], x = seq[j1];
+                const D4 vw = {x.x * w.x - x.y * w.y, x.x * w.y + x.y * w.x, x.z * w.x - x.w * w.y,
+                               x.z * w.y + x.w * w.x};
+                seq[j0] = D4{u.x + vw.x, u.y + vw.y, u.z + vw.z, u.w + vw.w};
+                seq[j1] = D4{u.x - vw.x, u.y - vw.y, u.z - vw.z, u.w - vw.w};
+                if (TD) {
+                    const double2 u2 = sq2[j0], x2 = sq2[j1];
+                    const double2 t = make_double2(x2.x * w.x - x2.y * w.y, x2.x * w.y + x2.y * w.x);
+                    sq2[j0] = make_double2(u2.x + t.x, u2.y + t.y);
+                    sq2[j1] = make_double2(u2.x - t.x, u2.y - t.y);
+                }
+            }
+            __syncthreads();
+        }
+    }
+    for (int i = threadIdx.x; i < RL; i += kNodeRowThreads) {
+        D4 o = {0.0, 0.0, 0.0, 0.0};
+        double2 o2 = make_double2(0.0, 0.0);
+        int lm = (i - (M / 2 + kNuHalf)) % M;   // l mod M, l = -M/2 - 3 .. M/2 + 4
+        if (lm < 0) lm += M;
+        if (pow2) {
+            o = seq[lm];
+            if (TD) o2 = sq2[lm];
+        } else {
+            int kk = (int)(((long long)(M - S / 2) * lm) % M);   // (s - S/2) l mod M at s = 0
+            for (int s = 0; s < S; s++) {
+                const double2 t = tw[kk];
+                const D4 h = seq[s];
+                o.x = fma(h.x, t.x, fma(-h.y, t.y, o.x));
+                o.y = fma(h.x, t.y, fma(h.y, t.x, o.y));
+                o.z = fma(h.z, t.x, fma(-h.w, t.y, o.z));
+                o.w = fma(h.z, t.y, fma(h.w, t.x, o.w));
+                if (TD) {
+                    const double2 h2 = sq2[s];
+                    o2.x = fma(h2.x, t.x, fma(-h2.y, t.y, o2.x));
+                    o2.y = fma(h2.x, t.y, fma(h2.y, t.x, o2.y));
+                }
+                kk += lm;
+                if (kk >= M) kk -= M;
+            }
+        }
+        out[i] = make_float4((float)o.x, (float)o.y, (float)o.z, (float)o.w);
+        if (TD) out2[i] = make_float2((float)o2.x, (float)o2.y);
+    }
+}
+
+// Node rows per LDS stage: at most 60 KiB (all 6 or 7 rows at 256 samples
+// without taudot rows), so that two blocks share a CU.
+__host__ __device__ inline int node_stage(int S, int q, bool td) {
+    return max(1, min(q, 61440 / (nu_row_len(S) * (td ? 24 : 16))));
+}
+
+// One work item of the node form: kNodePPL paths per lane; per antenna the
+// tap weights and the phase factor once, then per node the kNu8W taps (16-byte
+// LDS reads, 8 more for the taudot rows) times the node's Lagrange polynomial.
+// Bound by those LDS reads: 8 q (16 or 24) bytes per path and antenna.
+template <bool TD>
+__device__ __forceinline__ void adj_item_node(const AdjArgs &a, float4 *rsh, const int P, const int grp,
+                                              const int blk_p0) {
+    constexpr int PPL = kNodePPL;
+    const auto amp = gmem(a.rec.amp);
+    const auto bet = gmem(a.rec.beta);
+    const auto eps = gmem(a.rec.epsd);
+    const auto alp = gmem(a.rec.alpha);
+    const auto gam = gmem(a.rec.gamma);
+    const auto tbar = gmem(a.tau_bar);
+    int pp[PPL];
+    bool act[PPL];
+    float Ax[PPL], Ay[PPL], beta[PPL], epsd[PPL], abr[PPL], abi[PPL], tdb[PPL], tau[PPL], lp[PPL];
+    const int S = a.S, RL = nu_row_len(S), Q = a.nd.q;
+    const double cb = (double)a.nd.cbar;
+    const int stage = node_stage(S, Q, TD);
+    float2 *rs2 = reinterpret_cast<float2 *>(rsh + stage * RL);
+#pragma unroll
+    for (int i = 0; i < PPL; i++) {
+        pp[i] = blk_p0 + i * kNodeThreads + (int)threadIdx.x;
+        act[i] = pp[i] < P;
+        const int pc = act[i] ? pp[i] : blk_p0;
+        const F2 A = amp[pc];
+        Ax[i] = A.x;
+        Ay[i] = A.y;
+        beta[i] = bet[pc];
+        epsd[i] = eps[pc];
+        abr[i] = abi[i] = tdb[i] = 0.0f;
+        pp[i] = pc;
+        tau[i] = node_offset(beta[i], a.nd.nu0f, a.nd.inv_h);   // [-1, 1]
+        lp[i] = 1.0f;
+        for (int k = 0; k < Q; k++) lp[i] *= node_factor(tau[i], a.nd.node[k].x);
+    }
+    const int v0 = grp * a.v_per, v1 = min(a.V, v0 + a.v_per);
+    for (int v = v0; v < v1; v++) {
+        float zc[PPL], zs[PPL], w[PPL][kNu8W], pr[PPL], pi[PPL], qr[PPL], qi[PPL], tr[PPL], ti[PPL];
+        int i0[PPL];
+#pragma unroll
+        for (int i = 0; i < PPL; i++) {
+            const float alpha = alp[(size_t)v * a.rec.cap + pp[i]];
+            const float gamma = gam[(size_t)v * a.rec.cap + pp[i]];
+            const NodePoint pt = node_point(alpha, exact_gamma(alpha, gamma, a.nd.kappa, a.nd.inv_kappa), beta[i],
+                                            epsd[i], cb, S);
+            const double xf = floor(pt.x);
+            i0[i] = min(max((int)xf + S, 0), 2 * S);   // row index of the first tap xf - 3 (clamped: NaN-safe)
+            nu8_weights((float)(pt.x - xf - 0.5), w[i]);
+            zs[i] = pt.zi;
+            zc[i] = pt.zr;
+            pr[i] = pi[i] = qr[i] = qi[i] = tr[i] = ti[i] = 0.0f;
+        }
+        const auto rows_v = gmem4(a.nu_rows) + (size_t)v * Q * RL;
+        for (int q0 = 0; q0 < Q; q0 += stage) {
+            const int nr = min(stage, Q - q0);
+            __syncthreads();   // the previous stage has been read
+            for (int i = threadIdx.x; i < nr * RL; i += kNodeThreads) {
+                const F4 u = rows_v[(size_t)q0 * RL + i];
+                rsh[i] = make_float4(u.x, u.y, u.z, u.w);
+            }
+            if (TD) {
+                const auto t_v = gmem(a.td_rows) + ((size_t)v * Q + q0) * RL;
+                for (int i = threadIdx.x; i < nr * RL; i += kNodeThreads) {
+                    const F2 u = t_v[i];
+                    rs2[i] = make_float2(u.x, u.y);
+                }
+            }
+            __syncthreads();
+            for (int k = 0; k < nr; k++) {
+                const float2 nd = a.nd.node[q0 + k];
+#pragma unroll
+                for (int i = 0; i < PPL; i++) {
+                    const float4 *row = rsh + k * RL + i0[i];
+                    float sx = 0.f, sy = 0.f, sz = 0.f, sw = 0.f, tx = 0.f, ty = 0.f;
+#pragma unroll
+                    for (int t = 0; t < kNu8W; t++) {
+                        const float4 u = row[t];
+                        sx = fmaf(w[i][t], u.x, sx);
+                        sy = fmaf(w[i][t], u.y, sy);
+                        sz = fmaf(w[i][t], u.z, sz);
+                        sw = fmaf(w[i][t], u.w, sw);
+                    }
+                    if (TD) {
+                        const float2 *row2 = rs2 + k * RL + i0[i];
+#pragma unroll
+                        for (int t = 0; t < kNu8W; t++) {
+                            const float2 u = row2[t];
+                            tx = fmaf(w[i][t], u.x, tx);
+                            ty = fmaf(w[i][t], u.y, ty);
+                        }
+                    }
+                    const float Lq = lp[i] * nd.y * __builtin_amdgcn_rcpf(0.5f * node_factor(tau[i], nd.x));
+                    pr[i] = fmaf(Lq, sx, pr[i]);
+                    pi[i] = fmaf(Lq, sy, pi[i]);
+                    qr[i] = fmaf(Lq, sz, qr[i]);
+                    qi[i] = fmaf(Lq, sw, qi[i]);
+                    if (TD) {
+                        tr[i] = fmaf(Lq, tx, tr[i]);
+                        ti[i] = fmaf(Lq, ty, ti[i]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PPL; i++) {
+            // Q0 = z P, m = z Q (z = e^{2 pi j (alpha + cbar nu + g S/2)})
+            const float q0r = zc[i] * pr[i] - zs[i] * pi[i], q0i = zc[i] * pi[i] + zs[i] * pr[i];
+            const float mr = zc[i] * qr[i] - zs[i] * qi[i], mi = zc[i] * qi[i] + zs[i] * qr[i];
+            abr[i] += q0r;
+            abi[i] -= q0i;
+            if (act[i]) tbar[(size_t)v * a.rec.cap + pp[i]] = -2.0f * (float)kPi * (Ax[i] * mi + Ay[i] * mr);
+            if (TD) {
+                const float nr2 = zc[i] * tr[i] - zs[i] * ti[i], ni = zc[i] * ti[i] + zs[i] * tr[i];
+                tdb[i] = fmaf(-2.0f * (float)kPi, Ax[i] * ni + Ay[i] * nr2, tdb[i]);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < PPL; i++)
+        if (act[i]) {
+            gmem(a.abar_part)[(size_t)grp * a.rec.cap + pp[i]] = F2{abr[i], abi[i]};
+            if (TD) gmem(a.tdb_part)[(size_t)grp * a.rec.cap + pp[i]] = tdb[i];
+        }
+}
+
 // Path-stationary adjoint of Eq. (8).  For each (path, v, c) the sums
 //   P(x) = sum_s conj(G_s) x^s,  P'(x)   with x = e^{2 pi j delta}
 // run by Horner's rule; with z0 = e^{2 pi j phi0}:
@@ -430,18 +735,20 @@ __device__ __forceinline__ void adj_item(const AdjArgs &a, float2 *gsh, const in
 }
 
 // Work items of each request of a batch: (antenna groups) x (path tiles of
-// 256 x args[i].ppl paths) for its device-side path count; item_first[i] =
-// first item of request i, item_first[n] = total.  Also clears the work
-// counters of both adjoint forms.  One block.
+// args[i].tile paths) for its device-side path count; item_first[i] = first
+// item of request i, item_first[n] = total.  Also clears the work counters of
+// the adjoint forms and the requests' sums over rays.  One block.
 __global__ __launch_bounds__(1024) void k_adj_items(const AdjArgs *args, int n, uint32_t *item_first,
                                                     uint32_t *queue) {
     __shared__ uint32_t part[1024];
     const int t = threadIdx.x;
     const int chunk = (n + 1023) / 1024;
     const int b = t * chunk, e = min(n, b + chunk);
+    for (int i = 0; i < n; i++)
+        if (args[i].acc && t < args[i].n_acc) args[i].acc[t] = 0.0;
     uint32_t sum = 0;
     for (int i = b; i < e; i++) {
-        const uint32_t P = (uint32_t)args[i].count[0], tile = 256u * (uint32_t)args[i].ppl;
+        const uint32_t P = (uint32_t)args[i].count[0], tile = (uint32_t)args[i].tile;
         sum += (P + tile - 1u) / tile * (uint32_t)args[i].nvs;
     }
     part[t] = sum;
@@ -455,13 +762,14 @@ __global__ __launch_bounds__(1024) void k_adj_items(const AdjArgs *args, int n, 
     uint32_t run = part[t] - sum;
     for (int i = b; i < e; i++) {
         item_first[i] = run;
-        const uint32_t P = (uint32_t)args[i].count[0], tile = 256u * (uint32_t)args[i].ppl;
+        const uint32_t P = (uint32_t)args[i].count[0], tile = (uint32_t)args[i].tile;
         run += (P + tile - 1u) / tile * (uint32_t)args[i].nvs;
     }
     if (t == 1023) item_first[n] = part[1023];
     if (t == 0) {
         queue[0] = 0u;
         queue[kAdjQueueDirect] = 0u;
+        queue[kAdjQueueNode] = 0u;
     }
 }
 
@@ -529,6 +837,30 @@ __global__ __launch_bounds__(256) void k_synth_adj_nu(const AdjArgs *__restrict_
     }
 }
 
+// The same work queue over requests [r0, r1) for the node form; the work-item
+// word lies after the largest stage (float4 offset `slot`).
+template <bool TD>
+__global__ __launch_bounds__(kNodeThreads) void k_synth_adj_node(const AdjArgs *__restrict__ args,
+                                                                 const uint32_t *__restrict__ item_first, int r0,
+                                                                 int r1, uint32_t *queue, int slot) {
+    extern __shared__ float4 rsh[];
+    uint32_t &s_item = *reinterpret_cast<uint32_t *>(rsh + slot);
+    const uint32_t first = item_first[r0], total = item_first[r1];
+    for (;;) {
+        __syncthreads();   // the previous item is done with s_item and the rows
+        if (threadIdx.x == 0) s_item = first + atomicAdd(queue, 1u);
+        __syncthreads();
+        const uint32_t item = __builtin_amdgcn_readfirstlane(s_item);
+        if (item >= total) break;   // uniform over the block
+        const int lo = adj_request(item_first, r0, r1, item);
+        const AdjArgs &a = args[lo];
+        const int P = __builtin_amdgcn_readfirstlane(*gmem(a.count));
+        const uint32_t tiles = (uint32_t)((P + a.tile - 1) / a.tile);
+        const uint32_t local = item - item_first[lo];
+        adj_item_node<TD>(a, rsh, P, (int)(local / tiles), (int)(local % tiles) * a.tile);
+    }
+}
+
 __global__ void k_reduce_abar(const int32_t *count, const float2 *part, const float *tpart, int nvs, int cap,
                               float2 *abar, float *tdbar) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
@@ -538,11 +870,13 @@ __global__ void k_reduce_abar(const int32_t *count, const float2 *part, const fl
         float2 x = part[(size_t)s * cap + p];
         r += x.x;
         i += x.y;
-        t += tpart[(size_t)s * cap + p];
+        if (tpart) t += tpart[(size_t)s * cap + p];
     }
     abar[p] = make_float2(r, i);
-    tdbar[p] = t;
+    if (tpart) tdbar[p] = t;
 }
+
+constexpr int kParamSums = 16;
 
 struct GeomArgs {
     const float *verts;
@@ -561,13 +895,12 @@ struct GeomArgs {
     int32_t drop, exit_only;
     const float2 *abar;
     const float *tau_bar;   // [V][cap]
-    const float *tdbar;     // [cap] dL/d taudot
+    const float *tdbar;     // [cap] dL/d taudot, or NULL (no wanted gradient depends on it)
     int32_t cap;
     float *grad;            // [nv][3]
-    float *g_mats;          // [n_mats][2] or NULL
-    float *g_radar;         // [6] or NULL
-    float *g_rot;           // [9] or NULL
-    float *g_atten;         // [1] or NULL
+    double *acc;            // [kParamSums + 2 n_mats] sums over rays: origin (3), velocity
+                            // (3), rot (9), attenuation, materials; NULL: none wanted
+    int32_t want_mats, want_rot;
     int32_t attached;       // 1: first hits follow their triangle (Eqs. 6-7)
     float txl[SBR_MAX_TX][3];   // antenna positions in the radar frame
     float rxl[SBR_MAX_RX][3];
@@ -608,10 +941,10 @@ __device__ __forceinline__ float seg_sum(float x, int lane, int s0) {
 // coefficients included.  Rays of a wavefront are consecutive in a grid row,
 // so neighbouring lanes often hit the same face: their vertex gradients are
 // summed over runs of equal face ids first and added by one atomic per run.
+// The gradients summed over all rays (origin, velocity, rotation,
+// attenuation) are returned in sum[16] where wanted.
 template <int K>
-__global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63;
+__device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const int lane, float (&sum)[kParamSums]) {
     int first = 0, n = 0;               // n: bounces to recompute (last returning one + 1)
     uint32_t mask = 0;                  // bounces that return a path
     if (r < a.R) {
@@ -663,7 +996,7 @@ __global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
             const int mi = a.mat_id ? (int)a.mat_id[f] : 0;
             if (a.any_fresnel) {
                 reflect_coef(a.mt, mi, a.ch.fc, (double)CI[k], rc, drc);
-                if (a.g_mats) de = reflect_deps(a.mt, mi, a.ch.fc, (double)CI[k]);
+                if (a.want_mats) de = reflect_deps(a.mt, mi, a.ch.fc, (double)CI[k]);
                 if (mi < a.mt.n && a.mt.mode[mi] != 0) MAT[k] = mi;
             }
             RC[k] = make_float2((float)rc.re, (float)rc.im);
@@ -683,7 +1016,7 @@ __global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
     float gR[9];                            // dL/d rot from the antenna positions
 #pragma unroll
     for (int q = 0; q < 9; q++) gR[q] = 0.0f;
-    const bool want_rot = a.g_rot != nullptr;
+    const bool want_rot = a.want_rot != 0;
     float wJ = 0.0f;                        // sum over the ray's paths of Re(conj(Abar) A)
     const float atn = (float)a.rd.atten;
     float ga_atn = 0.0f;                    // dL/d attenuation
@@ -744,7 +1077,7 @@ __global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
                         if (i != j) ex = make_float2(ex.x * RC[i].x - ex.y * RC[i].y, ex.x * RC[i].y + ex.y * RC[i].x);
                     const float2 dA = make_float2(ex.x * DRC[j].x - ex.y * DRC[j].y, ex.x * DRC[j].y + ex.y * DRC[j].x);
                     cib[j] += ab.x * dA.x + ab.y * dA.y;
-                    if (a.g_mats) {
+                    if (a.want_mats) {
                         // eps_c = eps_r - j sigma / (omega eps_0): d/deps_r = d/deps_c,
                         // d/dsigma = -j / (omega eps_0) d/deps_c
                         const float2 W = make_float2(ex.x * DEPS[j].x - ex.y * DEPS[j].y,
@@ -805,7 +1138,7 @@ __global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
             }
             go = go - (Rb / Rk) * (X[k] - O);        // R_k = |x_k - origin|
             // taudot = 2 (u . d_1) / c
-            const float tdq = a.tdbar[p] * 2.0f * ic0;
+            const float tdq = a.tdbar ? a.tdbar[p] * 2.0f * ic0 : 0.0f;
             gu = gu + tdq * f3((float)d0[0], (float)d0[1], (float)d0[2]);
             gd0 = gd0 + tdq * U;
 #pragma unroll
@@ -902,7 +1235,7 @@ __global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
             atomic_add3(a.grad, a.faces[3 * f + 1], f3(v9[3], v9[4], v9[5]));
             atomic_add3(a.grad, a.faces[3 * f + 2], f3(v9[6], v9[7], v9[8]));
         }
-        if (a.g_mats) {
+        if (a.want_mats) {
             // one wavefront sum per distinct material of this bounce
             const int km = act ? MAT[j] : -1;
             uint64_t pending = __ballot(km >= 0);
@@ -910,46 +1243,71 @@ __global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
                 const int leader = __ffsll((unsigned long long)pending) - 1;
                 const int m = __shfl(km, leader);
                 const bool mine = km == m;
-                float e0 = mine ? gm[j].x : 0.0f, e1 = mine ? gm[j].y : 0.0f;
+                double e0 = mine ? (double)gm[j].x : 0.0, e1 = mine ? (double)gm[j].y : 0.0;
                 for (int off = 32; off >= 1; off >>= 1) {
                     e0 += __shfl_xor(e0, off);
                     e1 += __shfl_xor(e1, off);
                 }
                 if (lane == leader) {
-                    atomicAdd(&a.g_mats[2 * m], e0);
-                    atomicAdd(&a.g_mats[2 * m + 1], e1);
+                    atomicAdd(&a.acc[kParamSums + 2 * m], e0);
+                    atomicAdd(&a.acc[kParamSums + 2 * m + 1], e1);
                 }
                 pending &= ~__ballot(mine);
             }
         }
     }
-    if (a.g_radar) {
-        float v6[6] = {go.x, go.y, go.z, gu.x, gu.y, gu.z};
-#pragma unroll
-        for (int q = 0; q < 6; q++) {
-            for (int off = 32; off >= 1; off >>= 1) v6[q] += __shfl_xor(v6[q], off);
-            if (lane == 0) atomicAdd(&a.g_radar[q], v6[q]);
-        }
-    }
-    if (a.g_atten) {
-        float v = ga_atn;
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0) atomicAdd(a.g_atten, v);
-    }
-    if (want_rot) {
+    if (a.acc) {
         // d_0 = rot d_local: dL/drot += (dL/dd_0) d_local^T, where dL/dd_0 is
-        // what the reverse sweep left for the first segment plus the Doppler part
+        // what the reverse sweep left for the first segment plus the Doppler part;
+        // zb = rot e_z: the gains add dL/dzb to the third column
         const float3 g0 = dnext + gd0;
         const float l0 = (float)dl[0], l1 = (float)dl[1], l2 = (float)dl[2];
-        // zb = rot e_z: the gains add dL/dzb to the third column
-        float v9[9] = {gR[0] + g0.x * l0, gR[1] + g0.x * l1, gR[2] + g0.x * l2 + gZ.x,
-                       gR[3] + g0.y * l0, gR[4] + g0.y * l1, gR[5] + g0.y * l2 + gZ.y,
-                       gR[6] + g0.z * l0, gR[7] + g0.z * l1, gR[8] + g0.z * l2 + gZ.z};
+        const float v16[kParamSums] = {go.x, go.y, go.z, gu.x, gu.y, gu.z,
+                                       gR[0] + g0.x * l0, gR[1] + g0.x * l1, gR[2] + g0.x * l2 + gZ.x,
+                                       gR[3] + g0.y * l0, gR[4] + g0.y * l1, gR[5] + g0.y * l2 + gZ.y,
+                                       gR[6] + g0.z * l0, gR[7] + g0.z * l1, gR[8] + g0.z * l2 + gZ.z, ga_atn};
 #pragma unroll
-        for (int q = 0; q < 9; q++) {
-            for (int off = 32; off >= 1; off >>= 1) v9[q] += __shfl_xor(v9[q], off);
-            if (lane == 0) atomicAdd(&a.g_rot[q], v9[q]);
-        }
+        for (int q = 0; q < kParamSums; q++) sum[q] = v16[q];
+    }
+}
+
+// The sums over rays are taken in FP64 (wavefronts, the block, then one atomic
+// per block and sum into a.acc): they cancel, and in FP32 their value depended
+// on the order of the atomics at 1e-6.
+template <int K>
+__global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
+    __shared__ double sh[4][kParamSums];
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    float sum[kParamSums];
+#pragma unroll
+    for (int q = 0; q < kParamSums; q++) sum[q] = 0.0f;
+    geom_ray<K>(a, r, lane, sum);
+    if (!a.acc) return;   // uniform over the grid
+#pragma unroll
+    for (int q = 0; q < kParamSums; q++) {
+        double d = (double)sum[q];
+        for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off);
+        if (lane == 0) sh[w][q] = d;
+    }
+    __syncthreads();
+    if (threadIdx.x < kParamSums)
+        atomicAdd(&a.acc[threadIdx.x],
+                  (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]));
+}
+
+// The parameter gradients wanted += the sums over rays.
+__global__ void k_param_add(const double *acc, int n_mats, float *g_mats, float *g_radar, float *g_rot,
+                            float *g_atten) {
+    const int q = threadIdx.x;
+    if (q < 6) {
+        if (g_radar) g_radar[q] += (float)acc[q];
+    } else if (q < 15) {
+        if (g_rot) g_rot[q - 6] += (float)acc[q];
+    } else if (q == 15) {
+        if (g_atten) g_atten[0] += (float)acc[q];
+    } else if (q < kParamSums + 2 * n_mats) {
+        if (g_mats) g_mats[q - kParamSums] += (float)acc[q];
     }
 }
 
@@ -981,6 +1339,7 @@ struct BackExtra {
     float *tau_bar;
     float2 *part, *abar;
     float *tpart, *tdbar;
+    double *acc;
     float *corr;
     float4 *rows;
     size_t bytes;
@@ -996,6 +1355,7 @@ static BackExtra back_extra(void *buf, int32_t R, int32_t K, int32_t V, int32_t 
     e.abar = cv.take<float2>(cap);
     e.tpart = cv.take<float>((size_t)bp.nvs * cap);
     e.tdbar = cv.take<float>(cap);
+    e.acc = cv.take<double>(kParamSums + 2 * SBR_MAX_MATERIALS);
     e.corr = nullptr;
     e.rows = nullptr;
     if (nu_size(S)) {
@@ -1016,7 +1376,8 @@ struct AdjTable {
     AdjArgs *args;
     uint32_t *item_first;
     uint32_t *queue;
-    int32_t *row_first;   // first G row of each request of the non-uniform FFT form
+    int32_t *row_first;   // first G row of each request of the chirp-row form
+    int32_t *node_first;  // first node row of each request of the node form
 };
 
 static AdjTable adj_table(void *buf, int n, size_t *bytes) {
@@ -1026,6 +1387,7 @@ static AdjTable adj_table(void *buf, int n, size_t *bytes) {
     t.item_first = cv.take<uint32_t>((size_t)n + 1);
     t.queue = cv.take<uint32_t>(64);
     t.row_first = cv.take<int32_t>((size_t)n + 1);
+    t.node_first = cv.take<int32_t>((size_t)n + 1);
     if (bytes) *bytes = align_up(cv.off, 256);
     return t;
 }
@@ -1042,23 +1404,34 @@ static int adj_rows(int Sp) { return std::max(1, std::min<int>(kAdjRowsMax, (655
 
 int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream_t s) {
     if (n <= 0) return SBR_OK;
-    // requests of the non-uniform FFT form first, then those of the direct one
+    // requests of the node form first, then those of the chirp-row form, then
+    // those of the direct one
+    std::vector<NodePlan> plans(n);
     std::vector<int> order;
     for (int r = 0; r < n; r++)
-        if (use_nu(reqs[r].cd.S, reqs[r].flags)) order.push_back(r);
+        if (use_nu(reqs[r].cd.S, reqs[r].flags)) plans[r] = node_plan(reqs[r].rd, reqs[r].gd, reqs[r].cd);
+    for (int r = 0; r < n; r++)
+        if (plans[r].q) order.push_back(r);
+    const int n_node = (int)order.size();
+    for (int r = 0; r < n; r++)
+        if (!plans[r].q && use_nu(reqs[r].cd.S, reqs[r].flags)) order.push_back(r);
     const int n_nu = (int)order.size();
     for (int r = 0; r < n; r++)
         if (!use_nu(reqs[r].cd.S, reqs[r].flags)) order.push_back(r);
     std::vector<AdjArgs> aa(n);
     std::vector<GeomArgs> gg(n);
     size_t lds_f2 = 0;   // float2 words of the largest G-row stage
-    long long items_nu = 0, items_direct = 0;
+    long long items_node = 0, items_nu = 0, items_direct = 0;
+    bool any_td = false;
     for (int r = 0; r < n; r++) {
         const BackwardReq &q = reqs[order[r]];
         const RadarDev &rd = q.rd;
         const int V = rd.n_tx * rd.n_rx;
         const long long cap = q.st.rec.cap;
-        const bool nu = r < n_nu;
+        const bool node = r < n_node, nu = r < n_nu;
+        // the taudot adjoint reaches the velocity, the ray directions and,
+        // through the attached first hit, the vertices
+        const bool td = (q.flags & SBR_ATTACHED) || (q.params && (q.params->radar || q.params->rot));
         BackPlan bp = back_plan(cap, V);
         const BackExtra e = back_extra(q.extra, q.gd.nx * q.gd.ny, q.gd.K, V, q.cd.C, q.cd.S);
         AdjArgs &a = aa[r];
@@ -1070,7 +1443,7 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         a.S = q.cd.S;
         a.v_per = bp.v_per;
         a.nvs = bp.nvs;
-        a.ppl = nu ? kNuPPL : kAdjPPL;
+        a.tile = node ? kNodeThreads * kNodePPL : nu ? 256 * kNuPPL : 256 * kAdjPPL;
         a.fcf = (float)q.cd.fc;
         a.sl_fs = (float)(q.cd.slope / q.cd.fs);
         a.tc = (float)q.cd.tc;
@@ -1079,13 +1452,21 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         a.tdb_part = e.tpart;
         a.nu_rows = nu ? e.rows : nullptr;
         a.nu_corr = nu ? e.corr : nullptr;
+        a.nd = plans[order[r]];
+        // node rows with taudot sums take 24 bytes per point of q <= C / 2 rows:
+        // within the chirp rows' 16 bytes of C rows
+        a.td_rows = node ? reinterpret_cast<float2 *>(e.rows + (size_t)V * a.nd.q * nu_row_len(a.S)) : nullptr;
+        if (node && td) any_td = true;   // then made for every node-form request of the batch
         a.Sp = (q.cd.S + 7) / 8 * 8;
         a.rows = adj_rows(a.Sp);
-        if (nu) {
-            items_nu += (cap + 256 * kNuPPL - 1) / (256 * kNuPPL) * bp.nvs;
+        const long long items = (cap + a.tile - 1) / a.tile * bp.nvs;
+        if (node) {
+            items_node += items;
+        } else if (nu) {
+            items_nu += items;
         } else {
             lds_f2 = std::max(lds_f2, (size_t)a.rows * a.Sp);
-            items_direct += (cap + 256 * kAdjPPL - 1) / (256 * kAdjPPL) * bp.nvs;
+            items_direct += items;
         }
         GeomArgs &g = gg[r];
         const sbr_mesh *m = q.mesh;
@@ -1108,13 +1489,15 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         g.exit_only = (q.flags & SBR_EXIT_ONLY) ? 1 : 0;
         g.abar = e.abar;
         g.tau_bar = e.tau_bar;
-        g.tdbar = e.tdbar;
+        g.tdbar = td ? e.tdbar : nullptr;
         g.cap = (int32_t)cap;
         g.grad = q.grad;
-        g.g_mats = q.params ? q.params->materials : nullptr;
-        g.g_radar = q.params ? q.params->radar : nullptr;
-        g.g_rot = q.params ? q.params->rot : nullptr;
-        g.g_atten = q.params ? q.params->attenuation : nullptr;
+        const bool want = q.params && (q.params->materials || q.params->radar || q.params->rot || q.params->attenuation);
+        g.acc = want ? e.acc : nullptr;
+        g.want_mats = q.params && q.params->materials;
+        g.want_rot = q.params && q.params->rot;
+        a.acc = g.acc;
+        a.n_acc = kParamSums + 2 * q.mt.n;
         g.attached = (q.flags & SBR_ATTACHED) ? 1 : 0;
         for (int t = 0; t < SBR_MAX_TX; t++)
             for (int c = 0; c < 3; c++) g.txl[t][c] = t < q.radar->n_tx ? (float)q.radar->tx[t][c] : 0.0f;
@@ -1126,35 +1509,78 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
     if (rc) return rc;
     hipLaunchKernelGGL(k_adj_items, dim3(1), dim3(1024), 0, s, t.args, n, t.item_first, t.queue);
     SBR_LAUNCHED();
-    if (n_nu > 0) {
-        // all requests of this form: 1/Psi tables, then the row transforms
+    // gradient rows of requests [r0, r1) of one of the FFT forms in row_first[0..]
+    auto put_rows = [&](int r0, int r1, int32_t *dst, unsigned *total, int *max_s) {
         std::vector<int32_t> row_first(1, 0);
-        int max_s = 0;
-        for (int r = 0; r < n_nu; r++) {
-            const long long rows = (long long)aa[r].V * aa[r].C;
+        *max_s = 0;
+        for (int r = r0; r < r1; r++) {
+            const long long rows = (long long)aa[r].V * (aa[r].nd.q ? aa[r].nd.q : aa[r].C);
             if (row_first.back() + rows > 0x7fffffffLL) {
                 set_error("batched backward: more than 2^31 gradient rows in one launch");
-                return SBR_E_ARG;
+                return (int)SBR_E_ARG;
             }
             row_first.push_back(row_first.back() + (int32_t)rows);
-            max_s = std::max(max_s, (int)aa[r].S);
+            *max_s = std::max(*max_s, (int)aa[r].S);
         }
-        if ((rc = put_table(t.row_first, row_first.data(), sizeof(int32_t) * (n_nu + 1), s))) return rc;
+        *total = (unsigned)row_first.back();
+        return put_table(dst, row_first.data(), sizeof(int32_t) * row_first.size(), s);
+    };
+    if (n_node > 0) {
+        unsigned rows = 0;
+        int max_s = 0;
+        if ((rc = put_rows(0, n_node, t.node_first, &rows, &max_s))) return rc;
         ProfScope ps(kProfSynthAdj, s);
-        hipLaunchKernelGGL(k_nu_corr_adj, dim3((unsigned)((max_s + 255) / 256), (unsigned)n_nu), dim3(256), 0, s,
-                           t.args);
+        // sequences and twiddles, and the chirp groups' partial sums where a
+        // row has fewer columns than the block threads (at most 144 KiB)
+        const size_t lds_rows = (size_t)2 * max_s * (any_td ? 64 : 48) + kNodeRowThreads * 32;
+        size_t slot = 0;   // float4 words of the largest stage
+        for (int r = 0; r < n_node; r++) {
+            const int RL = nu_row_len(aa[r].S);
+            slot = std::max(slot, (size_t)(node_stage(aa[r].S, aa[r].nd.q, any_td) * RL * (any_td ? 24 : 16) + 15) / 16);
+        }
+        const size_t lds = sizeof(float4) * slot + 16;
+        const void *kr = any_td ? (const void *)k_node_adj_rows<true> : (const void *)k_node_adj_rows<false>;
+        const void *kt = any_td ? (const void *)k_synth_adj_node<true> : (const void *)k_synth_adj_node<false>;
+        if (lds_rows > 65536 - 1024)
+            SBR_HIP(hipFuncSetAttribute(kr, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_rows));
+        const dim3 grid((unsigned)std::max(1LL, std::min<long long>(items_node,
+                                                                   resident_blocks(kt, kNodeThreads, lds, 256 * 2))));
+        if (any_td)
+            hipLaunchKernelGGL(k_node_adj_rows<true>, dim3(rows), dim3(kNodeRowThreads), lds_rows, s, t.args,
+                               t.node_first, n_node);
+        else
+            hipLaunchKernelGGL(k_node_adj_rows<false>, dim3(rows), dim3(kNodeRowThreads), lds_rows, s, t.args,
+                               t.node_first, n_node);
+        SBR_LAUNCHED();
+        ProfScope pk(kProfNuTaps, s);
+        if (any_td)
+            hipLaunchKernelGGL(k_synth_adj_node<true>, grid, dim3(kNodeThreads), lds, s, t.args, t.item_first, 0,
+                               n_node, t.queue + kAdjQueueNode, (int)slot);
+        else
+            hipLaunchKernelGGL(k_synth_adj_node<false>, grid, dim3(kNodeThreads), lds, s, t.args, t.item_first, 0,
+                               n_node, t.queue + kAdjQueueNode, (int)slot);
+    }
+    SBR_LAUNCHED();
+    if (n_nu > n_node) {
+        // all requests of the chirp-row form: 1/Psi tables, then the row transforms
+        unsigned rows = 0;
+        int max_s = 0;
+        if ((rc = put_rows(n_node, n_nu, t.row_first, &rows, &max_s))) return rc;
+        ProfScope ps(kProfSynthAdj, s);
+        hipLaunchKernelGGL(k_nu_corr_adj, dim3((unsigned)((max_s + 255) / 256), (unsigned)(n_nu - n_node)), dim3(256),
+                           0, s, t.args + n_node);
         const size_t lds_rows = sizeof(float4) * 2 * max_s + sizeof(float2) * 2 * max_s;   // sequence + twiddles
-        hipLaunchKernelGGL(k_nu_rows, dim3((unsigned)row_first.back()), dim3(256), lds_rows, s, t.args, t.row_first,
-                           n_nu);
+        hipLaunchKernelGGL(k_nu_rows, dim3(rows), dim3(256), lds_rows, s, t.args + n_node, t.row_first,
+                           n_nu - n_node);
         SBR_LAUNCHED();
         size_t slot = 0;   // float4 words of the largest row stage
-        for (int r = 0; r < n_nu; r++) slot = std::max(slot, (size_t)nu_stage(aa[r].S) * nu_row_len(aa[r].S));
+        for (int r = n_node; r < n_nu; r++) slot = std::max(slot, (size_t)nu_stage(aa[r].S) * nu_row_len(aa[r].S));
         const size_t lds = sizeof(float4) * slot + 16;
         dim3 grid((unsigned)std::max(1LL, std::min<long long>(items_nu, resident_blocks((const void *)k_synth_adj_nu<kNuPPL>,
                                                                                          256, lds, 256 * 2))));
         ProfScope pk(kProfNuTaps, s);
-        hipLaunchKernelGGL(k_synth_adj_nu<kNuPPL>, grid, dim3(256), lds, s, t.args, t.item_first, 0, n_nu, t.queue,
-                           (int)slot);
+        hipLaunchKernelGGL(k_synth_adj_nu<kNuPPL>, grid, dim3(256), lds, s, t.args, t.item_first, n_node, n_nu,
+                           t.queue, (int)slot);
     }
     SBR_LAUNCHED();
     if (n_nu < n) {
@@ -1172,7 +1598,8 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         const GeomArgs &g = gg[r];
         const long long cap = a.rec.cap;
         hipLaunchKernelGGL(k_reduce_abar, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, a.count, a.abar_part,
-                           a.tdb_part, a.nvs, (int)cap, const_cast<float2 *>(g.abar), const_cast<float *>(g.tdbar));
+                           g.tdbar ? a.tdb_part : nullptr, a.nvs, (int)cap, const_cast<float2 *>(g.abar),
+                           const_cast<float *>(g.tdbar));
         SBR_LAUNCHED();
         if (g.R == 0 || g.nf == 0) continue;
         dim3 gb((unsigned)((g.R + 255) / 256));
@@ -1185,6 +1612,11 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         case 6: hipLaunchKernelGGL(k_geom_adj<6>, gb, dim3(256), 0, s, g); break;
         case 7: hipLaunchKernelGGL(k_geom_adj<7>, gb, dim3(256), 0, s, g); break;
         default: hipLaunchKernelGGL(k_geom_adj<8>, gb, dim3(256), 0, s, g); break;
+        }
+        if (g.acc) {
+            const sbr_param_grads &pg = *reqs[order[r]].params;
+            hipLaunchKernelGGL(k_param_add, dim3(1), dim3(256), 0, s, g.acc, g.mt.n, pg.materials, pg.radar, pg.rot,
+                               pg.attenuation);
         }
         SBR_LAUNCHED();
     }

@@ -15,6 +15,11 @@ through these weights and through exact psi values differ by under 1e-7 of
 sum |h| (S = 64 and 256), while either is about 2e-7 of sum |h| from the
 direct sum.
 
+The adjoint over Doppler nodes uses the kernel of width W = 8, beta = 2.3 W
+(nu_weights8.h): x = xf + 1/2 + u (xf = floor(x), u in [-1/2, 1/2]), taps at
+l = xf - 3 + t, t = 0..7, w_t(u) = psi(u + 7/2 - t) = E_t(u^2) + u O_t(u^2) and
+w_{7-t} = E_t(u^2) - u O_t(u^2), t = 0..3, degree 6 and 7 in u (within 9e-8).
+
 Run from the repository root: python paper_2311_13182_amd/csrc/gen_nu_weights.py
 """
 from __future__ import annotations
@@ -56,6 +61,55 @@ def fit():
     return E, O, err
 
 
+NE8, NO8 = 4, 4
+
+
+def psi8(d: np.ndarray) -> np.ndarray:
+    x = 2.0 * d / 8
+    out = np.zeros_like(d, dtype=np.float64)
+    m = np.abs(x) < 1.0
+    out[m] = np.exp(2.30 * 8 * (np.sqrt(1.0 - x[m] ** 2) - 1.0))
+    return out
+
+
+def fit8():
+    u = np.linspace(-0.5, 0.5, 40001)
+    u2 = u * u
+    E = np.zeros((4, NE8))
+    O = np.zeros((4, NO8))
+    err = 0.0
+    for t in range(4):
+        y = psi8(u + 3.5 - t)
+        E[t] = np.linalg.lstsq(np.vander(u2, NE8, increasing=True), 0.5 * (y + y[::-1]), rcond=None)[0]
+        O[t] = np.linalg.lstsq(u[:, None] * np.vander(u2, NO8, increasing=True), 0.5 * (y - y[::-1]), rcond=None)[0]
+        approx = np.vander(u2, NE8, increasing=True) @ E[t] + u * (np.vander(u2, NO8, increasing=True) @ O[t])
+        err = max(err, float(np.max(np.abs(approx - y))))
+    return E, O, err
+
+
+def header8(E: np.ndarray, O: np.ndarray, err: float) -> str:
+    def rows(A):
+        return ",\n".join("    {" + ", ".join(f"{v:.9e}f" for v in c) + "}" for c in A)
+    return "\n".join([
+        "// Generated by gen_nu_weights.py (do not edit): least-squares polynomial",
+        "// forms of the 8 tap weights of the exponential-of-semicircle kernel of width",
+        "// 8, beta = 18.40, in the offset u in [-1/2, 1/2] from the middle between two",
+        "// grid points: w_t = E_t(u^2) + u O_t(u^2), w_{7-t} = E_t(u^2) - u O_t(u^2)",
+        "// (t < 4); coefficients by ascending power of u^2.  Largest deviation from",
+        f"// the kernel on the fitting grid: {err:.2e}.",
+        "#pragma once",
+        "",
+        f"constexpr int kNu8PolyNE = {NE8}, kNu8PolyNO = {NO8};   // coefficients per polynomial",
+        f"constexpr float kNu8PolyE[4][{NE8}] = {{",
+        rows(E),
+        "};",
+        f"constexpr float kNu8PolyO[4][{NO8}] = {{",
+        rows(O),
+        "};",
+        "",
+    ])
+
+
 def header(E: np.ndarray, O: np.ndarray, err: float) -> str:
     def row(c):
         return "{" + ", ".join(f"{v:.9e}f" for v in c) + "}"
@@ -86,6 +140,11 @@ def main():
     path = os.path.join(HERE, "nu_weights.h")
     with open(path, "w") as f:
         f.write(text)
+    print(f"wrote {path} (max deviation {err:.2e})")
+    E, O, err = fit8()
+    path = os.path.join(HERE, "nu_weights8.h")
+    with open(path, "w") as f:
+        f.write(header8(E, O, err))
     print(f"wrote {path} (max deviation {err:.2e})")
 
 

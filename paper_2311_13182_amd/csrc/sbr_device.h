@@ -3,6 +3,7 @@
 
 #include "sbr_internal.h"
 #include "nu_weights.h"
+#include "nu_weights8.h"
 
 namespace sbr {
 
@@ -208,6 +209,85 @@ __device__ __forceinline__ void nu_weights(float u, float w[kNuW]) {
             w[kNuW - 1 - t] = fmaf(-u, o, e);
         }
     }
+}
+
+// 2 (tau - x_j), the factor of a Doppler node (NodePlan) in the product
+// lp = prod_j 2 (tau - x_j) = 2 T_q(tau): the node's Lagrange polynomial is
+// L_j = lp node[j].y / (tau - x_j).  Never zero: at a node the factor cancels
+// against itself.
+__device__ __forceinline__ float node_factor(float tau, float x) {
+    const float d = tau - x;
+    return 2.0f * (d == 0.0f ? 1e-20f : d);
+}
+
+// The width-8 kernel (beta = 2.3 W) of the node form's adjoint: taps
+// psi8(u + 7/2 - t) for x = floor(x) + 1/2 + u (nu_weights8.h), and its
+// deconvolution (as nu_corr_value).
+constexpr int kNu8W = 8;
+constexpr int kNu8Taps = kNu8W * kNuSteps / 2;
+__device__ inline double nu8_kernel_sample(int n) {
+    const double x = 2.0 * n / (double)(kNu8W * kNuSteps);
+    return exp(2.30 * kNu8W * (sqrt(1.0 - x * x) - 1.0));
+}
+__device__ inline double nu8_corr_value(int S, int s, const double *kn) {
+    const double c1 = cospi(2.0 * (double)(s - S / 2) / (double)(2 * S * kNuSteps));
+    double cp = 1.0, cc = c1, acc = kn[0] + 2.0 * kn[1] * c1;
+    for (int n = 2; n < kNu8Taps; n++) {
+        const double cn = 2.0 * c1 * cc - cp;
+        cp = cc;
+        cc = cn;
+        acc += 2.0 * kn[n] * cn;
+    }
+    return (double)kNuSteps / acc;
+}
+__device__ __forceinline__ void nu8_weights(float u, float w[kNu8W]) {
+    const float u2 = u * u;
+#pragma unroll
+    for (int t = 0; t < kNu8W / 2; t++) {
+        float e = kNu8PolyE[t][kNu8PolyNE - 1], o = kNu8PolyO[t][kNu8PolyNO - 1];
+#pragma unroll
+        for (int k = kNu8PolyNE - 2; k >= 0; k--) e = fmaf(e, u2, kNu8PolyE[t][k]);
+#pragma unroll
+        for (int k = kNu8PolyNO - 2; k >= 0; k--) o = fmaf(o, u2, kNu8PolyO[t][k]);
+        w[t] = fmaf(u, o, e);
+        w[kNu8W - 1 - t] = fmaf(-u, o, e);
+    }
+}
+
+// Where a path meets the rows of the node form: its grid coordinate x = 2S g,
+// g = gamma + cbar eps reduced to [-1/2, 1/2], and its phase factor z = e^{2
+// pi j (alpha + cbar beta + g S/2)}.  One such point stands for all chirps of
+// an antenna, so its phase is formed in FP64 and its sine and cosine by the
+// library function: the chirp rows' rounding of each chirp's own phase, and
+// the hardware sine's, average over the chirps, this one's would not.
+struct NodePoint {
+    double x;
+    float zr, zi;
+};
+__device__ __forceinline__ NodePoint node_point(float alpha, double gamma, float beta, float epsd, double cb, int S) {
+    const double f = fma(cb, (double)epsd, gamma);
+    double th = fma((double)(S / 2), f, fma(cb, (double)beta, (double)alpha));
+    th -= rint(th);
+    NodePoint p;
+    p.x = (f - rint(f)) * (double)(2 * S);
+    sincospif(2.0f * (float)th, &p.zi, &p.zr);
+    return p;
+}
+
+// gamma = kappa fc tau of a path record to FP64: fc tau = n + alpha, where the
+// integer n follows from the rounded gamma while fc tau is below 2^22 cycles
+// (8 km at 77 GHz).  The record's own rounding (2e-6 rad over the samples of a
+// target at 1.6 m) would otherwise be the largest error of the adjoint sums.
+__device__ __forceinline__ double exact_gamma(float alpha, float gamma, double kappa, double inv_kappa) {
+    const double cyc = (double)gamma * inv_kappa;
+    if (inv_kappa == 0.0 || !(fabs(cyc) < 4194304.0)) return (double)gamma;
+    return kappa * (rint(cyc - (double)alpha) + (double)alpha);
+}
+
+// Offset of a path's Doppler frequency from the nodes' centre, in half widths.
+__device__ __forceinline__ float node_offset(float beta, float nu0, float inv_h) {
+    const float d = beta - nu0;
+    return (d - rintf(d)) * inv_h;
 }
 
 }  // namespace sbr

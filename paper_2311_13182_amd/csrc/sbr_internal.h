@@ -144,7 +144,8 @@ struct PathSoA {
 
 // Scratch layout of the path stage (compaction + records).
 struct PathStage {
-    int32_t *count;       // [4]: [0] = number of paths P
+    int32_t *count;       // [0] = number of paths P, [1] = float bits of the largest
+                          // max(|Re A|, |Im A|) over them
     int32_t *ray_first;   // [R + 1] first path index of each ray
     int32_t *blk;         // [nblk] per-block path counts then offsets
     int32_t nblk;
@@ -153,11 +154,36 @@ struct PathStage {
 
 constexpr int kPathBlock = 256;   // rays per block of the compaction kernels
 
+// Doppler nodes of the node form of the non-uniform FFT sums.  With nu =
+// fc t_chirp taudot (cycles per chirp) and kappa = slope / (fs fc), the phase
+// of Eq. (8) in cycles is
+//   alpha + c nu + s gamma + c s eps,  eps = kappa nu
+//     = [alpha + cbar nu] + s [gamma + cbar eps] + (c - cbar)(1 + s kappa) nu.
+// Only the last term couples the chirps to a path, and every path of a request
+// has nu = (2 fc t_chirp / c0) u . d within the range that the ray grid's
+// directions d span: for a scene speed u of a few m/s the term turns by less
+// than a cycle between the ends of that range.  So it is interpolated in nu
+// from q Chebyshev nodes nu_j = nu0 + h x_j: a path spreads into (or reads) q
+// grid rows instead of one row per chirp, and the chirps are formed from the
+// q rows at the end with the exact factor e^{2 pi j (c - cbar)(1 + s kappa) nu_j}.
+constexpr int kMaxNodes = 32;
+struct NodePlan {
+    int32_t q;       // nodes; 0: the chirp-row form is used
+    int32_t cbar;    // C / 2
+    double nu0, h;   // centre and half width of the range of nu
+    double kappa;
+    double inv_kappa;   // 1 / kappa (0 with no slope)
+    float nu0f;      // nu0 modulo 1
+    float inv_h;     // 1 / h (0 with one node)
+    float2 node[kMaxNodes];   // x_j and the weight (-1)^j sin(theta_j) / (2 q) of its Lagrange polynomial
+};
+
 // Launch shape of the IF synthesis: L samples per lane, SB sample blocks per
 // chirp row, tiles_per_v wavefronts per antenna, n_chunks path chunks.
 struct SynthPlan {
     int32_t L, SB, tiles_per_v, n_chunks;
-    int32_t nu, cg;      // non-uniform FFT form (L = 0): chirps per spreading block
+    int32_t nu, cg;      // non-uniform FFT form (L = 0): chirps (nodes) per spreading block
+    int32_t q, dup;      // node form: nodes (0: chirp rows), copies of each row in LDS
 };
 
 // A pointer read from a device table is generic; marking it global lets the
@@ -178,6 +204,10 @@ struct F2 {
 };
 __device__ __forceinline__ SBR_GLOBAL_AS const F2 *gmem(const float2 *p) { return (SBR_GLOBAL_AS const F2 *)p; }
 __device__ __forceinline__ SBR_GLOBAL_AS F2 *gmem(float2 *p) { return (SBR_GLOBAL_AS F2 *)p; }
+struct alignas(16) D2 {
+    double x, y;
+};
+__device__ __forceinline__ SBR_GLOBAL_AS D2 *gmem2(double2 *p) { return (SBR_GLOBAL_AS D2 *)p; }
 
 // Arguments of one request's IF synthesis (device-table entry of a batch).
 struct SynthArgs {
@@ -196,15 +226,25 @@ struct SynthArgs {
     float *corr;         // [S]
     long long *grid;     // [n_chunks][V][C][re, im][nu_row_len(S)]
     float2 *out;         // [V][C][S] the IF cube (set by launch_synth_batch)
+    // node form (nd.q > 0): cg nodes per spreading block, ncg node groups, the
+    // fixed-point bits below the largest amplitude, the transformed rows; the
+    // grids are [n_chunks][V][q][re, im][nu_row_len(S)]
+    int32_t dup, bits;
+    double2 *modes;      // [V][q][S] deconvolved modes of each node row
+    NodePlan nd;
 };
 
 PathStage carve_path_stage(Carver &cv, int32_t R, int32_t K, int32_t V);
+// The Doppler nodes of a request; q = 0 where the chirp-row form is used.
+NodePlan node_plan(const RadarDev &rd, const GridDev &g, const ChirpDev &ch);
 SynthPlan synth_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S, bool nu);
+// The node form's plan: never more grid words than synth_plan(..., true) asks for.
+SynthPlan synth_node_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S, int32_t q);
 size_t synth_partial_elems(const SynthPlan &p, int32_t V, int32_t C, int32_t S);
 // Fixed-point grid words (long long) of the non-uniform FFT form.
 size_t synth_grid_words(const SynthPlan &p, int32_t V, int32_t C, int32_t S);
-SynthArgs synth_args(const PathStage &st, const SynthPlan &p, int32_t V, int32_t C, int32_t S, float2 *partial,
-                     long long *grid, float *corr, uint32_t *amax);
+SynthArgs synth_args(const PathStage &st, const SynthPlan &p, const NodePlan &nd, int32_t V, int32_t C, int32_t S,
+                     float2 *partial, long long *grid, float *corr, uint32_t *amax);
 // Device-table bytes of a batch of n syntheses.
 size_t synth_table_bytes(int n);
 // IF synthesis of n requests whose path stages are enqueued: one launch per

@@ -90,24 +90,32 @@ __global__ __launch_bounds__(1024) void k_path_scan(PathArgs a) {
     }
     if (t == 1023) {
         a.st.count[0] = part[1023];
+        a.st.count[1] = 0;   // amplitude bound, raised by k_path_refine
         a.st.ray_first[a.R] = part[1023];
+    }
+}
+
+// Raises *bound to the block's largest m (bits of a non-negative float, so
+// the integer order is the float order); every thread of the block calls it.
+// Most blocks find a bound that already covers theirs and send no atomic.
+__device__ __forceinline__ void block_raise(uint32_t m, uint32_t *bound, uint32_t *sh) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < (int)(blockDim.x >> 6); w++) m = max(m, sh[w]);
+        if (m > __hip_atomic_load(bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(bound, m);
     }
 }
 
 __device__ __forceinline__ double frac_d(double x) { return x - floor(x); }
 
-__global__ __launch_bounds__(kPathBlock) void k_path_refine(PathArgs a) {
-    __shared__ int sh[kPathBlock / 64];
-    const size_t r = (size_t)blockIdx.x * kPathBlock + threadIdx.x;
-    const bool act = r < (size_t)a.R;
-    int nb = 0;
-    const uint32_t mask = act ? ray_mask(a, r, &nb) : 0u;
-    const int n = __popc(mask);
-    int incl = block_incl_scan(n, sh);
-    if (!act) return;
-    int p = a.st.blk[blockIdx.x] + incl - n;
-    a.st.ray_first[r] = p;
-    if (n == 0) return;
+// Records of ray r's returning bounces (mask, the last one below nb) from
+// path p on; returns the bits of their largest max(|Re A|, |Im A|).
+__device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r, const uint32_t mask, const int nb,
+                                               int p) {
+    uint32_t amax = 0;
     const int ix = (int)(r % a.g.nx), iy = (int)(r / a.g.nx);
     double d[3], dw;
     grid_ray(a.g, a.rd, ix, iy, d, &dw);
@@ -168,7 +176,10 @@ __global__ __launch_bounds__(kPathBlock) void k_path_refine(PathArgs a) {
             const double cr = ((x[0] - a.rd.o[0]) * zb[0] + (x[1] - a.rd.o[1]) * zb[1] + (x[2] - a.rd.o[2]) * zb[2]) / Rk;
             sc *= pow(ct > 0.0 ? ct : 0.0, a.rd.n_tg) * pow(cr > 0.0 ? cr : 0.0, a.rd.n_rg);
         }
-        a.st.rec.amp[p] = make_float2((float)(pr.re * sc), (float)(pr.im * sc));
+        const float2 A = make_float2((float)(pr.re * sc), (float)(pr.im * sc));
+        amax = max(amax, __float_as_uint(fmaxf(fabsf(A.x), fabsf(A.y))));
+        if (A.x != A.x || A.y != A.y) amax = 0x7fc00000u;   // fmaxf drops a NaN
+        a.st.rec.amp[p] = A;
         a.st.rec.beta[p] = (float)beta;
         a.st.rec.epsd[p] = (float)epsd;
         // one square root per (TX, RX) pair instead of per-antenna distance
@@ -194,6 +205,20 @@ __global__ __launch_bounds__(kPathBlock) void k_path_refine(PathArgs a) {
             d[i] = d[i] - 2.0 * dn * N[i] / nl;
         }
     }
+    return amax;
+}
+
+__global__ __launch_bounds__(kPathBlock) void k_path_refine(PathArgs a) {
+    __shared__ int sh[kPathBlock / 64];
+    const size_t r = (size_t)blockIdx.x * kPathBlock + threadIdx.x;
+    const bool act = r < (size_t)a.R;
+    int nb = 0;
+    const uint32_t mask = act ? ray_mask(a, r, &nb) : 0u;
+    const int n = __popc(mask);
+    const int p = a.st.blk[blockIdx.x] + block_incl_scan(n, sh) - n;
+    if (act) a.st.ray_first[r] = p;
+    const uint32_t amax = n > 0 ? refine_ray(a, r, mask, nb, p) : 0u;
+    block_raise(amax, reinterpret_cast<uint32_t *>(a.st.count) + 1, reinterpret_cast<uint32_t *>(sh));
 }
 
 }  // namespace
@@ -679,6 +704,21 @@ __device__ __forceinline__ int rint_product(float a, float b) {
     return __float_as_int(fmaf(a, b, 12582912.0f)) - 0x4B400000;
 }
 
+// The power of two that scales amplitudes below 2^e to below 2^bits (the bits
+// of the largest one as for nu_scale).
+__device__ __forceinline__ int nu_exponent(int bits, uint32_t amax_bits) {
+    int e = 0;
+    const float amax = __uint_as_float(amax_bits);
+    if (amax > 0.0f && amax_bits < 0x7f800000u) (void)frexpf(amax, &e);
+    return bits - max(e, -100);
+}
+
+// rint(a b) for |a b| < 2^51 as a 64-bit integer (the fused a b + 1.5 2^52
+// holds it in its low mantissa bits; the constant's low 32 bits are zero).
+__device__ __forceinline__ unsigned long long rint_word(double a, double b) {
+    return (unsigned long long)__double_as_longlong(fma(a, b, 6755399441055744.0)) - 0x4338000000000000ull;
+}
+
 constexpr int kNuSpreadThreads = 1024;
 
 // Spreading: block = (path chunk, antenna v, group of cg chirps).  A
@@ -928,6 +968,234 @@ __global__ __launch_bounds__(256) void k_nu_synth_rows(const SynthArgs *__restri
     }
 }
 
+// ---- the node form of Eq. (8)'s type-1 transform ---------------------------
+// With the Doppler nodes of NodePlan (sbr_internal.h) and the Lagrange
+// polynomials L_j over them, row (v, c) of the cube is
+//   sum_j e^{2 pi j (c - cbar)(1 + s kappa) nu_j} F_j[v][s],
+//   F_j[v][s] = sum_p L_j(nu_p) A_p e^{2 pi j (alpha + cbar nu_p)} e^{2 pi j s g_p},  g_p = gamma + cbar eps,
+// so a path is spread into q rows of 2S points (q = 6 for the 2048^2-ray scene
+// at 1 m/s) instead of one row per chirp (128 there).
+// k_node_spread: block = (path chunk, antenna, group of cg nodes).  Real and
+// imaginary parts are separate 64-bit integer cells in LDS, contributions
+// rounded at 2^bits over the largest amplitude of the request (bits >= 31, 36
+// for that scene), so the sums are exact, in any order, without emptying the
+// cells on the way: nothing is held back for carries as in a packed word, and
+// the rounding (2^-36 of the largest amplitude) is far below single precision.
+// A product w_t (L_j A z) of two floats is exact in FP64; the fused add of
+// 1.5 2^52 rounds it to an integer held in the low mantissa bits.
+// What bounds it is the rate of 64-bit LDS atomics (14 q per path and
+// antenna), so the order of a lane's 7 q cells is chosen as in k_nu_spread: the
+// first cell of lane l lies on bank pair l mod 32 and additions to one cell
+// by one instruction stay rare.  Rows are RLs = 7 (mod 32) bank pairs apart,
+// so cell (row, j + t) is on bank pair 7 row + t + j; with e = (l - j) mod 32 a
+// lane starts at row e / 7 and tap e % 7 and walks the taps and then the nodes
+// cyclically.  With fewer than 5 nodes each row is held in `dup` copies, so
+// that the starting rows still differ between lanes.
+__device__ __forceinline__ int node_row_stride(int RL) { return RL + ((7 - RL) & 31); }
+
+__global__ __launch_bounds__(1024) void k_node_spread(const SynthArgs *__restrict__ args,
+                                                      const int32_t *__restrict__ didx,
+                                                      const int32_t *__restrict__ first, int m) {
+    extern __shared__ unsigned long long nsp[];
+    __shared__ float2 tab[kMaxNodes];
+    const int j = nu_request(first, m, (int)blockIdx.x);
+    const SynthArgs &a = args[didx[j]];
+    const int blk = (int)blockIdx.x - first[j];
+    const int S = a.S, RL = nu_row_len(S), RLs = node_row_stride(RL);
+    const int gi = blk % a.ncg, rest = blk / a.ncg;
+    const int v = rest % a.V, chunk = rest / a.V;
+    const int q_lo = gi * a.cg, nq = min(a.cg, a.nd.q - q_lo);
+    const int rows = nq * a.dup, plane = rows * RLs, tid = (int)threadIdx.x;
+    for (int i = tid; i < 2 * plane; i += 1024) nsp[i] = 0ull;
+    if (tid < a.nd.q) tab[tid] = a.nd.node[tid];
+    __syncthreads();
+    const int P = __builtin_amdgcn_readfirstlane(*gmem(a.count));
+    const long long per = ((long long)P + a.n_chunks - 1) / a.n_chunks;
+    const int p0 = (int)min((long long)P, per * chunk);
+    const int p1 = (int)min((long long)P, per * (chunk + 1));
+    const int shift = nu_exponent(a.bits, (uint32_t)gmem(a.count)[1]);
+    const auto al = gmem(a.rec.alpha + (size_t)v * a.rec.cap);
+    const auto ga = gmem(a.rec.gamma + (size_t)v * a.rec.cap);
+    const auto amp = gmem(a.rec.amp);
+    const auto bet = gmem(a.rec.beta);
+    const auto eps = gmem(a.rec.epsd);
+    const double cb = (double)a.nd.cbar;
+    const int Q = a.nd.q;
+    const int lane = tid & 63;
+    for (int p = p0 + tid; p < p1; p += 1024) {
+        const float alpha = al[p], gamma = ga[p], beta = bet[p], epsd = eps[p];
+        const F2 A = amp[p];
+        const NodePoint pt = node_point(alpha, (double)gamma, beta, epsd, cb, S);
+        const double xr = rint(pt.x);
+        const int j0 = min(max((int)xr + S, 0), 2 * S);   // cell of the first tap xr - 3 (clamped: NaN-safe)
+        const float tau = node_offset(beta, a.nd.nu0f, a.nd.inv_h);   // [-1, 1]
+        float lp = 1.0f;
+        for (int k = 0; k < Q; k++) lp *= node_factor(tau, tab[k].x);
+        const float wr = ldexpf(A.x * pt.zr - A.y * pt.zi, shift);
+        const float wi = ldexpf(A.x * pt.zi + A.y * pt.zr, shift);
+        float w[kNuW];
+        nu_weights((float)(pt.x - xr), w);
+        const int e = (lane - j0) & 31;
+        int row = (e * 37) >> 8;        // e / 7
+        const int t0 = e - 7 * row;
+        row %= rows;
+        const int copy = row / nq;
+        int k = row - copy * nq;
+        // taps in the order t0, t0 + 1, ... (mod 7)
+        double wd[kNuW];
+        uint32_t off[kNuW];
+        {
+            float u[kNuW];
+#pragma unroll
+            for (int t = 0; t < kNuW; t++) u[t] = (t0 & 1) ? w[(t + 1) % kNuW] : w[t];
+#pragma unroll
+            for (int t = 0; t < kNuW; t++) w[t] = (t0 & 2) ? u[(t + 2) % kNuW] : u[t];
+#pragma unroll
+            for (int t = 0; t < kNuW; t++) u[t] = (t0 & 4) ? w[(t + 4) % kNuW] : w[t];
+#pragma unroll
+            for (int t = 0; t < kNuW; t++) {
+                wd[t] = (double)u[t];
+                off[t] = (uint32_t)(t0 + t >= kNuW ? t0 + t - kNuW : t0 + t);
+            }
+        }
+        for (int i = 0; i < nq; i++) {
+            const float2 nd = tab[q_lo + k];
+            const float Lq = lp * nd.y * __builtin_amdgcn_rcpf(0.5f * node_factor(tau, nd.x));
+            const double br = (double)(wr * Lq), bi = (double)(wi * Lq);
+            unsigned long long *cell = nsp + (copy * nq + k) * RLs + j0;
+#pragma unroll
+            for (int t = 0; t < kNuW; t++) {
+                atomicAdd(cell + off[t], rint_word(br, wd[t]));
+                atomicAdd(cell + plane + off[t], rint_word(bi, wd[t]));
+            }
+            k = k + 1 == nq ? 0 : k + 1;
+        }
+    }
+    __syncthreads();
+    // the chunk's rows [q][re, im][RL] of request j's partial
+    long long *dst = a.grid + (((size_t)chunk * a.V + v) * Q + q_lo) * (size_t)RL * 2;
+    for (int i = tid; i < nq * 2 * RL; i += 1024) {
+        const int r2 = i / RL, jj = i - r2 * RL;   // r2 = 2 node + (0: re, 1: im)
+        const unsigned long long *src = nsp + (r2 & 1) * plane + (r2 >> 1) * RLs + jj;
+        unsigned long long sum = 0ull;
+        for (int d = 0; d < a.dup; d++) sum += src[d * nq * RLs];
+        dst[i] = (long long)sum;
+    }
+}
+
+constexpr int kNodeRowThreads = 512;
+
+// Row (v, j) = blockIdx.x of the node form: the chunks' integer cells summed
+// (exact) and folded onto the periodic grid, scaled back to FP64, the DFT to
+// the S centred modes (as in k_nu_synth_rows) and the deconvolution 1/Psi:
+// F_j[v][s].  The 2S cells' real and imaginary sums are taken with several chunks' loads in flight (the fold is bound by their latency:
+// only V q rows exist).
+__global__ __launch_bounds__(kNodeRowThreads) void k_node_rows(const SynthArgs *__restrict__ args,
+                                                    const int32_t *__restrict__ didx,
+                                                    const int32_t *__restrict__ first, int m) {
+    extern __shared__ double2 nrs[];
+    __shared__ double kn[kNuTaps];
+    const int j = nu_request(first, m, (int)blockIdx.x);
+    const SynthArgs &a = args[didx[j]];
+    const int S = a.S, M = 2 * S, RL = nu_row_len(S);
+    double2 *b = nrs;        // [M]
+    double2 *tw = nrs + M;   // [M]
+    const size_t row = (size_t)((int)blockIdx.x - first[j]);
+    const double inv = ldexp(1.0, -nu_exponent(a.bits, (uint32_t)gmem(a.count)[1]));
+    const size_t chunk_stride = (size_t)a.V * a.nd.q * RL * 2;
+    const bool pow2 = (M & (M - 1)) == 0;
+    const int lg = 31 - __clz(M);
+    const auto src = gmem(a.grid) + row * RL * 2;   // real row, then imaginary row
+    for (int i = threadIdx.x; i < 2 * M; i += kNodeRowThreads) {
+        const int im = i >= M, l = i - im * M;
+        const int j1 = (l + M / 2 + kNuHalf) % M;
+        const auto s1 = src + im * RL + j1;
+        const bool wrap = j1 + M < RL - 1;
+        long long c = 0;
+#pragma unroll 8
+        for (int ch = 0; ch < a.n_chunks; ch++) c += s1[ch * chunk_stride];
+        if (wrap)
+            for (int ch = 0; ch < a.n_chunks; ch++) c += s1[ch * chunk_stride + M];
+        const int pos = pow2 ? (int)(__brev((uint32_t)l) >> (32 - lg)) : l;
+        (&b[pos].x)[im] = (double)c * inv;   // power-of-two scale
+    }
+    for (int k = threadIdx.x; k < M; k += kNodeRowThreads) {
+        double sn, cs;
+        sincospi(2.0 * k / M, &sn, &cs);
+        tw[k] = make_double2(cs, sn);
+    }
+    if (threadIdx.x < kNuTaps) kn[threadIdx.x] = nu_kernel_sample((int)threadIdx.x);
+    __syncthreads();
+    const auto out = gmem2(a.modes) + row * S;
+    if (pow2) {
+        // X[k] = sum_l b_l e^{2 pi j k l / M}, decimation in time
+        for (int half = 1; half < M; half <<= 1) {
+            const int tstep = M / (2 * half);
+            for (int i = threadIdx.x; i < M / 2; i += kNodeRowThreads) {
+                const int pos = i & (half - 1), j0 = ((i - pos) << 1) + pos, j1 = j0 + half;
+                const double2 w = tw[pos * tstep], u = b[j0], v = b[j1];
+                const double2 vw = make_double2(v.x * w.x - v.y * w.y, v.x * w.y + v.y * w.x);
+                b[j0] = make_double2(u.x + vw.x, u.y + vw.y);
+                b[j1] = make_double2(u.x - vw.x, u.y - vw.y);
+            }
+            __syncthreads();
+        }
+        for (int s = threadIdx.x; s < S; s += kNodeRowThreads) {
+            const double2 f = b[((s - S / 2) % M + M) % M];   // mode s' = s - S/2
+            const double cr = (double)nu_corr_value(S, s, kn);
+            out[s] = D2{f.x * cr, f.y * cr};
+        }
+        return;
+    }
+    for (int s = threadIdx.x; s < S; s += kNodeRowThreads) {
+        const int step = ((s - S / 2) % M + M) % M;   // s' mod M
+        int k = 0;
+        double fr = 0.0, fi = 0.0;
+        for (int l = 0; l < M; l++) {
+            const double2 t = tw[k], bb = b[l];
+            fr = fma(bb.x, t.x, fma(-bb.y, t.y, fr));
+            fi = fma(bb.x, t.y, fma(bb.y, t.x, fi));
+            k += step;
+            if (k >= M) k -= M;
+        }
+        const double cr = (double)nu_corr_value(S, s, kn);
+        out[s] = D2{fr * cr, fi * cr};
+    }
+}
+
+// Chirps from the node rows: out[v][c][s] = sum_j F_j[v][s] e^{2 pi j (c -
+// cbar)(1 + s kappa) nu_j}, the phase reduced in FP64; one thread per sample
+// (q cached 16-byte loads each; 393,216 threads at 12 x 128 x 256).  A
+// non-finite amplitude makes the cube NaN, as the direct sum would.
+__global__ __launch_bounds__(256) void k_node_chirps(const SynthArgs *__restrict__ args,
+                                                     const int32_t *__restrict__ didx,
+                                                     const int32_t *__restrict__ first, int m) {
+    __shared__ double nus[kMaxNodes];
+    const int j = nu_request(first, m, (int)blockIdx.x);
+    const SynthArgs &a = args[didx[j]];
+    const int Q = a.nd.q;
+    if ((int)threadIdx.x < Q)
+        nus[threadIdx.x] = a.nd.nu0 + a.nd.h * cospi((2.0 * threadIdx.x + 1.0) / (2.0 * Q));
+    __syncthreads();
+    const size_t i = (size_t)((int)blockIdx.x - first[j]) * 256 + threadIdx.x;
+    if (i >= (size_t)a.V * a.C * a.S) return;
+    const int s = (int)(i % a.S), vc = (int)(i / a.S), c = vc % a.C, v = vc / a.C;
+    const auto F = gmem2(a.modes) + (size_t)v * Q * a.S + s;
+    const double t = (double)(c - a.nd.cbar) * (1.0 + s * a.nd.kappa);
+    double re = 0.0, im = 0.0;
+    for (int k = 0; k < Q; k++) {
+        const double ph = t * nus[k];
+        float sn, cs;
+        sincospif(2.0f * (float)(ph - rint(ph)), &sn, &cs);
+        const D2 f = F[(size_t)k * a.S];
+        re += f.x * cs - f.y * sn;
+        im += f.x * sn + f.y * cs;
+    }
+    const bool bad = (uint32_t)gmem(a.count)[1] >= 0x7f800000u;
+    const float nan = __int_as_float(0x7fc00000);
+    gmem(a.out)[i] = bad ? F2{nan, nan} : F2{(float)re, (float)im};
+}
+
 }  // namespace
 
 __global__ void k_zero_f32(float *p, size_t n) {
@@ -993,6 +1261,94 @@ static SynthPlan nu_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S) 
     return p;
 }
 
+// Largest and smallest (U, W) -> (a U + b W + c) / sqrt(1 + U^2 + W^2) over
+// |U| <= hu, |W| <= hw: u . d over the ray grid's unit directions for the
+// velocity (a, b, c) in the radar frame.  The extremes lie at the interior
+// critical point (a / c, b / c), on an edge where its one-variable derivative
+// vanishes, or at a corner.
+static void direction_range(double a, double b, double c, double hu, double hw, double *lo, double *hi) {
+    *lo = INFINITY;
+    *hi = -INFINITY;
+    auto take = [&](double U, double W) {
+        U = std::min(std::max(U, -hu), hu);
+        W = std::min(std::max(W, -hw), hw);
+        const double f = (a * U + b * W + c) / std::sqrt(1.0 + U * U + W * W);
+        *lo = std::min(*lo, f);
+        *hi = std::max(*hi, f);
+    };
+    for (int i = 0; i < 2; i++) {
+        const double U = i ? hu : -hu, W = i ? hw : -hw;
+        take(U, -hw);
+        take(U, hw);
+        if (a * U + c != 0.0) take(U, b * (1.0 + U * U) / (a * U + c));
+        if (b * W + c != 0.0) take(a * (1.0 + W * W) / (b * W + c), W);
+    }
+    if (c != 0.0) take(a / c, b / c);
+}
+
+// The fewest nodes whose interpolation error, at most 4 sum_{k >= q} (x / 2)^k
+// / k! for phases within +-x (the Chebyshev coefficients of e^{j x t} are 2
+// J_k(x)), is below 1e-7: it is alike for neighbouring paths, so sums over
+// many paths that cancel would show a larger one.  From two chirps per node on
+// the node form reads fewer row points than the chirp rows (both directions
+// fit their buffers from there).
+NodePlan node_plan(const RadarDev &rd, const GridDev &g, const ChirpDev &ch) {
+    NodePlan n{};
+    if (!nu_size(ch.S) || ch.C < 2) return n;
+    double u[3];
+    for (int i = 0; i < 3; i++) u[i] = rd.rot[i] * rd.vel[0] + rd.rot[3 + i] * rd.vel[1] + rd.rot[6 + i] * rd.vel[2];
+    double lo, hi;
+    direction_range(u[0], u[1], u[2], g.thx, g.thy, &lo, &hi);
+    const double per = 2.0 * ch.fc * ch.tc / kC0;
+    n.nu0 = per * 0.5 * (lo + hi);
+    n.h = std::fabs(per) * 0.5 * (hi - lo);
+    n.kappa = ch.slope / (ch.fs * ch.fc);
+    n.inv_kappa = n.kappa != 0.0 ? 1.0 / n.kappa : 0.0;
+    n.cbar = ch.C / 2;
+    const double stretch = std::max(1.0, std::fabs(1.0 + (ch.S - 1) * n.kappa));
+    const double x = 2.0 * kPi * n.cbar * stretch * n.h;
+    if (!(x <= kMaxNodes) || !(std::fabs(n.nu0) < 1e6)) return n;   // also not-a-number
+    int q = 1;
+    for (; q <= kMaxNodes; q++) {
+        double term = 4.0, sum = 0.0;
+        for (int k = 1; k < q + 64; k++) {
+            term *= 0.5 * x / k;
+            if (k >= q) sum += term;
+        }
+        if (sum <= 1e-7) break;
+    }
+    if (2 * q > ch.C || q > kMaxNodes) return n;
+    n.q = q;
+    n.nu0f = (float)(n.nu0 - std::rint(n.nu0));
+    n.inv_h = q > 1 ? (float)(1.0 / n.h) : 0.0f;
+    for (int k = 0; k < q; k++) {
+        const double th = kPi * (2 * k + 1) / (2.0 * q);
+        n.node[k] = make_float2((float)std::cos(th), (float)((k & 1 ? -1.0 : 1.0) * std::sin(th) / (2.0 * q)));
+    }
+    return n;
+}
+
+// Node form: as many node rows per spreading block as 160 KiB of LDS hold (two
+// blocks then share a CU at 256 samples), path chunks for about two blocks
+// per CU, of at least 8192 path slots.  Its grids and transformed rows fit the
+// words that the chirp-row plan of the same sizes asks for (2 q <= C).
+SynthPlan synth_node_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S, int32_t q) {
+    SynthPlan p{};
+    p.nu = 1;
+    p.q = q;
+    const int RL = nu_row_len(S);
+    const long long row_bytes = 16LL * (RL + ((7 - RL) & 31));
+    const int fit = (int)std::max(1LL, (nu_lds_budget() - 1024) / row_bytes);
+    p.cg = std::min(q, fit);
+    p.dup = std::max(1, std::min((5 + p.cg - 1) / p.cg, fit / p.cg));
+    const long long ncg = (q + p.cg - 1) / p.cg, cap = (long long)R * K;
+    const long long want = (512 + (long long)V * ncg - 1) / ((long long)V * ncg);
+    const long long words = (long long)synth_grid_words(nu_plan(R, K, V, C, S), V, C, S);
+    const long long rows = 2LL * V * q * RL, modes = 2LL * V * q * S + 2;
+    p.n_chunks = (int32_t)std::max(1LL, std::min({want, (cap + 8191) / 8192, (words - modes) / rows}));
+    return p;
+}
+
 SynthPlan synth_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S, bool nu) {
     if (nu) return nu_plan(R, K, V, C, S);
     SynthPlan p{};
@@ -1029,8 +1385,8 @@ size_t synth_grid_words(const SynthPlan &p, int32_t V, int32_t C, int32_t S) {
     return p.nu ? (size_t)p.n_chunks * V * C * nu_row_len(S) * 2 : 0;
 }
 
-SynthArgs synth_args(const PathStage &st, const SynthPlan &p, int32_t V, int32_t C, int32_t S, float2 *partial,
-                     long long *grid, float *corr, uint32_t *amax) {
+SynthArgs synth_args(const PathStage &st, const SynthPlan &p, const NodePlan &nd, int32_t V, int32_t C, int32_t S,
+                     float2 *partial, long long *grid, float *corr, uint32_t *amax) {
     SynthArgs a{};
     a.count = st.count;
     a.rec = st.rec;
@@ -1044,36 +1400,63 @@ SynthArgs synth_args(const PathStage &st, const SynthPlan &p, int32_t V, int32_t
     a.partial = partial;
     a.nu = p.nu;
     a.cg = p.cg;
-    a.ncg = p.nu ? (C + p.cg - 1) / p.cg : 0;
+    a.ncg = p.nu ? ((p.q ? p.q : C) + p.cg - 1) / p.cg : 0;
     a.grid = grid;
     a.corr = corr;
     a.amax = amax;
+    if (p.q) {
+        a.nd = nd;
+        a.dup = p.dup;
+        // a row's sum over all path slots stays below 2^62 (|A psi L| < 2^(bits + 1))
+        int lg = 0;
+        while ((1LL << lg) < (long long)st.rec.cap) lg++;
+        a.bits = std::min(44, 60 - lg);
+        const size_t words = (size_t)2 * p.n_chunks * V * p.q * nu_row_len(S);
+        a.modes = reinterpret_cast<double2 *>(grid + align_up(words, 2));
+    }
     return a;
 }
 
 // Device table of a batched synthesis: the requests' arguments, then per
 // kernel form (VALU runs of L = 16, 32, 64 samples per lane; the matrix-core
-// form, L = 256) the requests using it and their first blocks.
+// form, L = 256) the requests using it and their first blocks; then the same
+// of the two non-uniform FFT forms (chirp rows, nodes).
 struct SynthTable {
     SynthArgs *args;
     int32_t *idx[4];
     int32_t *first[4];
-    int32_t *nidx;     // requests of the non-uniform FFT form
+    int32_t *nidx;     // requests of the chirp-row form
     int32_t *nfirst;   // their first spreading blocks
     int32_t *rfirst;   // their first cube rows
+    int32_t *didx;     // requests of the node form
+    int32_t *dfirst;   // their first spreading blocks
+    int32_t *drows;    // their first node rows
+    int32_t *dchirps;  // their first k_node_chirps blocks
 };
 
+// All arrays lie close together, so that one request's whole table is one
+// put_table launch.
 static SynthTable synth_table(void *buf, int n, size_t *bytes) {
     Carver cv(buf);
     SynthTable t;
     t.args = cv.take<SynthArgs>(n);
+    int32_t *w = cv.take<int32_t>((size_t)15 * (n + 1));
+    auto next = [&]() {
+        int32_t *p = w;
+        if (w) w += n + 1;
+        return p;
+    };
     for (int g = 0; g < 4; g++) {
-        t.idx[g] = cv.take<int32_t>(n);
-        t.first[g] = cv.take<int32_t>((size_t)n + 1);
+        t.idx[g] = next();
+        t.first[g] = next();
     }
-    t.nidx = cv.take<int32_t>(n);
-    t.nfirst = cv.take<int32_t>((size_t)n + 1);
-    t.rfirst = cv.take<int32_t>((size_t)n + 1);
+    t.nidx = next();
+    t.nfirst = next();
+    t.rfirst = next();
+    t.didx = next();
+    t.dfirst = next();
+    t.drows = next();
+    t.dchirps = next();
     if (bytes) *bytes = align_up(cv.off, 256);
     return t;
 }
@@ -1087,29 +1470,67 @@ size_t synth_table_bytes(int n) {
 int launch_synth_batch(const SynthArgs *args, const int *L, int n, void *table, float2 *const *out,
                        hipStream_t s) {
     if (n <= 0) return SBR_OK;
-    SynthTable t = synth_table(table, n, nullptr);
-    std::vector<SynthArgs> aa(args, args + n);
-    for (int i = 0; i < n; i++) aa[i].out = out[i];
-    int rc = put_table(t.args, aa.data(), sizeof(SynthArgs) * n, s);
-    if (rc) return rc;
+    // the table is filled in host memory and put on the device in one go
+    size_t bytes = 0;
+    const SynthTable t = synth_table(table, n, &bytes);
+    std::vector<char> image(bytes + 256, 0);
+    char *base = image.data() + (256 - (uintptr_t)image.data() % 256) % 256;
+    const SynthTable h = synth_table(base, n, nullptr);
+    for (int i = 0; i < n; i++) {
+        h.args[i] = args[i];
+        h.args[i].out = out[i];
+    }
+    // number of requests of each form; blocks of request k of a form start at first[k]
+    bool over = false;
+    auto add = [&](int32_t *first, int k, long long blocks) {
+        over |= first[k] + blocks > 0x7fffffffLL;
+        first[k + 1] = (int32_t)(first[k] + blocks);
+    };
     static const int kLs[4] = {16, 32, 64, kMfmaRun};
-    for (int g = 0; g < 4; g++) {
-        std::vector<int32_t> idx, first(1, 0);
-        for (int i = 0; i < n; i++) {
-            if (L[i] != kLs[g]) continue;
-            const long long blocks = (long long)args[i].gx * args[i].n_chunks;
-            if (first.back() + blocks > 0x7fffffffLL) {
-                set_error("batched synthesis: more than 2^31 blocks in one launch");
+    int md[4] = {0, 0, 0, 0}, mn = 0, mk = 0;
+    size_t lds_spread = 0, lds_rows = 0, lds_nspread = 0, lds_nrows = 0;
+    int max_s = 0, max_chunks = 1;
+    for (int i = 0; i < n && !over; i++) {
+        const SynthArgs &a = args[i];
+        const long long rows = (long long)a.V * a.C;
+        if (!a.nu) {
+            for (int g = 0; g < 4; g++) {
+                if (L[i] != kLs[g]) continue;
+                h.idx[g][md[g]] = i;
+                add(h.first[g], md[g]++, (long long)a.gx * a.n_chunks);
+            }
+        } else if (a.nd.q) {
+            const int RL = nu_row_len(a.S);
+            h.didx[mk] = i;
+            add(h.dfirst, mk, (long long)a.n_chunks * a.V * a.ncg);
+            add(h.drows, mk, (long long)a.V * a.nd.q);
+            add(h.dchirps, mk++, (rows * a.S + 255) / 256);
+            lds_nspread = std::max(lds_nspread, (size_t)16 * a.cg * a.dup * (RL + ((7 - RL) & 31)));
+            lds_nrows = std::max(lds_nrows, (size_t)2 * 2 * a.S * sizeof(double2));
+        } else {
+            if ((long long)a.cg * (nu_row_len(a.S) + 1) > (long long)kNuCells * kNuSpreadThreads) {
+                set_error("batched synthesis: spreading rows exceed the accumulators");
                 return SBR_E_ARG;
             }
-            idx.push_back(i);
-            first.push_back(first.back() + (int32_t)blocks);
+            h.nidx[mn] = i;
+            add(h.nfirst, mn, (long long)a.n_chunks * a.V * a.ncg);
+            add(h.rfirst, mn++, rows);
+            lds_spread = std::max(lds_spread, (size_t)a.cg * (nu_row_len(a.S) + 1) * 8);
+            lds_rows = std::max(lds_rows, (size_t)2 * 2 * a.S * sizeof(double2));
+            max_s = std::max(max_s, (int)a.S);
+            max_chunks = std::max(max_chunks, (int)a.n_chunks);
         }
-        if (idx.empty() || first.back() == 0) continue;
-        if ((rc = put_table(t.idx[g], idx.data(), sizeof(int32_t) * idx.size(), s))) return rc;
-        if ((rc = put_table(t.first[g], first.data(), sizeof(int32_t) * first.size(), s))) return rc;
-        const int m = (int)idx.size();
-        const dim3 grid((unsigned)first.back());
+    }
+    if (over) {
+        set_error("batched synthesis: more than 2^31 blocks in one launch");
+        return SBR_E_ARG;
+    }
+    int rc = put_table(table, base, bytes, s);
+    if (rc) return rc;
+    for (int g = 0; g < 4; g++) {
+        if (md[g] == 0 || h.first[g][md[g]] == 0) continue;
+        const int m = md[g];
+        const dim3 grid((unsigned)h.first[g][m]);
         ProfScope ps(kProfSynth, s);
         if (kLs[g] == kMfmaRun)
             hipLaunchKernelGGL(k_synth_mfma, grid, dim3(256), 0, s, t.args, t.first[g], t.idx[g], m);
@@ -1128,36 +1549,32 @@ int launch_synth_batch(const SynthArgs *args, const int *L, int n, void *table, 
                            args[i].n_chunks, e, out[i]);
     }
     SBR_LAUNCHED();
-    // the non-uniform FFT form, all its requests in five launches: amplitude
-    // words cleared, amplitude bounds, 1/Psi tables, spreading, row transforms
-    std::vector<int32_t> nidx, nfirst(1, 0), rfirst(1, 0);
-    size_t lds_spread = 0, lds_rows = 0;
-    int max_s = 0, max_chunks = 1;
-    for (int i = 0; i < n; i++) {
-        const SynthArgs &a = args[i];
-        if (!a.nu) continue;
-        const long long blocks = (long long)a.n_chunks * a.V * a.ncg, rows = (long long)a.V * a.C;
-        if (nfirst.back() + blocks > 0x7fffffffLL || rfirst.back() + rows > 0x7fffffffLL) {
-            set_error("batched synthesis: more than 2^31 blocks in one launch");
-            return SBR_E_ARG;
+    // the node form, all its requests in three launches: spreading, row
+    // transforms, chirps
+    if (mk > 0) {
+        ProfScope ps(kProfSynth, s);
+        if (lds_nspread > 65536 - 1024)
+            SBR_HIP(hipFuncSetAttribute((const void *)k_node_spread, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)lds_nspread));
+        {
+            ProfScope pk(kProfNuSpread, s);
+            hipLaunchKernelGGL(k_node_spread, dim3((unsigned)h.dfirst[mk]), dim3(1024), lds_nspread, s, t.args,
+                               t.didx, t.dfirst, mk);
         }
-        if ((long long)a.cg * (nu_row_len(a.S) + 1) > (long long)kNuCells * kNuSpreadThreads) {
-            set_error("batched synthesis: spreading rows exceed the accumulators");
-            return SBR_E_ARG;
-        }
-        nidx.push_back(i);
-        nfirst.push_back(nfirst.back() + (int32_t)blocks);
-        rfirst.push_back(rfirst.back() + (int32_t)rows);
-        lds_spread = std::max(lds_spread, (size_t)a.cg * (nu_row_len(a.S) + 1) * 8);
-        lds_rows = std::max(lds_rows, (size_t)2 * 2 * a.S * sizeof(double2));
-        max_s = std::max(max_s, (int)a.S);
-        max_chunks = std::max(max_chunks, (int)a.n_chunks);
+        SBR_LAUNCHED();
+        if (lds_nrows > 65536 - 1024)
+            SBR_HIP(hipFuncSetAttribute((const void *)k_node_rows, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)lds_nrows));
+        hipLaunchKernelGGL(k_node_rows, dim3((unsigned)h.drows[mk]), dim3(kNodeRowThreads), lds_nrows, s, t.args, t.didx,
+                           t.drows, mk);
+        hipLaunchKernelGGL(k_node_chirps, dim3((unsigned)h.dchirps[mk]), dim3(256), 0, s, t.args, t.didx,
+                           t.dchirps, mk);
+        SBR_LAUNCHED();
     }
-    if (!nidx.empty()) {
-        const int m = (int)nidx.size();
-        if ((rc = put_table(t.nidx, nidx.data(), sizeof(int32_t) * m, s))) return rc;
-        if ((rc = put_table(t.nfirst, nfirst.data(), sizeof(int32_t) * (m + 1), s))) return rc;
-        if ((rc = put_table(t.rfirst, rfirst.data(), sizeof(int32_t) * (m + 1), s))) return rc;
+    // the chirp-row form, all its requests in five launches: amplitude words
+    // cleared, amplitude bounds, 1/Psi tables, spreading, row transforms
+    if (mn > 0) {
+        const int m = mn;
         ProfScope ps(kProfSynth, s);
         hipLaunchKernelGGL(k_nu_zero, dim3((unsigned)m), dim3(256), 0, s, t.args, t.nidx);
         hipLaunchKernelGGL(k_nu_amax, dim3((unsigned)(kNuAmaxSub * max_chunks), (unsigned)m), dim3(256), 0, s,
@@ -1170,11 +1587,11 @@ int launch_synth_batch(const SynthArgs *args, const int *L, int n, void *table, 
                                         (int)lds_spread));
         {
             ProfScope pk(kProfNuSpread, s);
-            hipLaunchKernelGGL(k_nu_spread, dim3((unsigned)nfirst.back()), dim3(kNuSpreadThreads), lds_spread, s,
+            hipLaunchKernelGGL(k_nu_spread, dim3((unsigned)h.nfirst[m]), dim3(kNuSpreadThreads), lds_spread, s,
                                t.args, t.nidx, t.nfirst, m);
         }
         SBR_LAUNCHED();
-        hipLaunchKernelGGL(k_nu_synth_rows, dim3((unsigned)rfirst.back()), dim3(256), lds_rows, s, t.args, t.nidx,
+        hipLaunchKernelGGL(k_nu_synth_rows, dim3((unsigned)h.rfirst[m]), dim3(256), lds_rows, s, t.args, t.nidx,
                            t.rfirst, m);
         SBR_LAUNCHED();
     }

@@ -1,0 +1,67 @@
+"""The Doppler-node form of the non-uniform FFT sums (Eq. 8 and its adjoint)
+at the edges of its range, against the oracle's direct sums on the oracle's
+own hits and against the library's direct sums.
+
+Tolerance of the cube, per sample and relative to sum |I^s|: the tap kernel
+and its polynomial weights 2.5e-6, the node interpolation 1e-7, single
+precision weights and phases 1e-6, and the rounding of the path records'
+beat frequency and chirp phase, 2 pi (S gamma 2^-25 + C 2^-25).  The vertex
+gradient is compared with the direct sums' on the same records; both share
+those records, and the direct form's own single-precision rounding over up to
+1024 samples is what separates them (1e-4 up to 256 samples, 3e-4 above)."""
+import numpy as np
+import pytest
+
+from paper_2311_13182_amd import scenes as S
+from tests._parity import device_hits_from_oracle, log
+
+pytestmark = pytest.mark.gpu
+
+
+def _scene(C, Sn, n_tx, n_rx, vel, K=2):
+    v, f = S.superquadric_object(3, 20, 11, (0.3, 0.25, 0.2), (0.0, 0.05, 1.5))
+    th = S.fov_tan(0.32, 1.5)
+    return S.Scene("nodes", v.astype(np.float32), f.astype(np.int32), S.default_radar(n_tx, n_rx, vel=vel),
+                   S.Chirp(n_samples=Sn, n_chirps=C), S.Grid(40, 33, th, th, K))
+
+
+# (C, S, n_tx, n_rx, velocity): one node (static: copies of the row in LDS) to
+# many, the fewest chirps that take the form and one less, odd sizes, two node
+# groups per block (1024 samples), approaching and lateral scenes
+CASES = [(8, 256, 1, 4, (0, 0, 0)), (4, 16, 1, 1, (0, 0, 0)), (5, 17, 2, 1, (0, 0, 0)), (9, 31, 1, 2, (0, 0, 0.02)),
+         (64, 256, 3, 4, (0, 0, 1)), (50, 200, 2, 3, (2, 0, 1)), (128, 64, 1, 2, (-4, 1, -6)), (33, 1024, 1, 2, (0, 0, 1)),
+         (40, 1023, 1, 1, (3, 0, 0)), (256, 128, 1, 2, (0, 0, 15)), (17, 48, 1, 1, (0, 0, 1.0)), (16, 48, 1, 1, (0, 0, 1.0))]
+
+
+@pytest.mark.parametrize("C,Sn,n_tx,n_rx,vel", CASES)
+def test_nodes_match_the_direct_sums(C, Sn, n_tx, n_rx, vel):
+    import torch
+    from oracle import pyoracle as orc
+    from paper_2311_13182_amd.sbr import Simulator
+    sc = _scene(C, Sn, n_tx, n_rx, vel)
+    tr = orc.trace(sc)
+    p = orc.paths(sc, tr["tri"], tr["flags"])
+    ref = orc.synth(sc, p)
+    sim = Simulator(sc)
+    sim.hits = device_hits_from_oracle(tr)
+    got = sim.synth()
+    again = sim.synth()
+    assert torch.equal(got.view(torch.int32), again.view(torch.int32))
+    err = np.abs(torch.view_as_complex(got).cpu().numpy() - ref).max() / np.abs(p["amp"]).sum()
+    gam = sc.chirp.slope / sc.chirp.fs * 2 * 2.0 / S.C0
+    tol = 3.6e-6 + 2 * np.pi * (Sn * gam + C) * 2.0 ** -25
+    log(f"nodes C={C} S={Sn} vel={vel}: max error {err:.2e} of sum |I^s| (tolerance {tol:.2e})")
+    assert err <= tol
+
+    rng = np.random.default_rng(1)
+    G = torch.as_tensor(rng.normal(size=got.shape).astype(np.float32), device="cuda")
+    out = []
+    for direct in (False, True):
+        gr, gR = torch.zeros(6, device="cuda"), torch.zeros((3, 3), device="cuda")
+        gv = sim.backward(G, grad_radar=gr, grad_rot=gR, direct_sums=direct)
+        plain = sim.backward(G, direct_sums=direct)   # without the taudot sums
+        out.append([t.double().cpu() for t in (gv, plain, gr[:3], gr[3:], gR)])
+    tol = 3e-4 if Sn > 256 else 1e-4
+    for a, b, what in zip(*out, ("vertices", "vertices alone", "origin", "velocity", "rotation")):
+        e = float((a - b).norm() / b.norm())
+        assert e <= tol, f"{what}: {e:.2e}"
