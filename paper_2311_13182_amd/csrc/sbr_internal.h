@@ -61,19 +61,24 @@ struct Carver {
 };
 
 // ----------------------------------------------------------------- BVH
-// Node of the depth-first layout: box, escape index (next node after this
-// subtree; == node count ends traversal), leaf slot (-1 for internal nodes;
-// the left child of an internal node is the next node).
-struct __align__(32) BvhNode {
-    float lo[3];
-    float hi[3];
-    int32_t escape;
-    int32_t leaf;
+// Node of the depth-first layout, 16 bytes: the box in 16-bit steps of the
+// mesh's bounds (low half lo, high half hi, rounded outwards), and the link: an
+// internal node's escape index (next node after its subtree; == node count
+// ends traversal; its left child is the next node), a leaf's kLeafBit | slot
+// (its escape is the next node).
+struct __align__(16) BvhNode {
+    uint32_t x, y, z, link;
 };
+constexpr uint32_t kLeafBit = 0x80000000u;
 
 // Triangle of a leaf: three vertices, .w of the first = original face id bits.
 struct __align__(16) LeafTri {
     float4 a, b, c;
+};
+
+// Box of a run of leaves.
+struct Box {
+    float lo[3], hi[3];
 };
 
 struct BvhView {
@@ -82,13 +87,17 @@ struct BvhView {
     BvhNode *nodes;     // [n_nodes], depth-first order
     LeafTri *tris;      // [n], Morton order (leaf slot order)
     int32_t *order;     // [n] leaf slot -> original face
-    int32_t *parent;    // [n_nodes] radix-tree parent (tree indices; -1 root)
-    int2 *child;        // [n-1] radix-tree children
-    int32_t *dfs_of;    // [n_nodes] radix-tree index -> depth-first index
-    uint32_t *visits;   // [n-1] bottom-up arrival counters
+    int32_t *other;     // [n - 1] internal node i covers the leaf slots from i to other[i]
+    int32_t *dfs_of;    // [n_nodes] radix-tree index (internal i, leaf n - 1 + slot) -> depth-first index
+    Box *prefix;        // [n] union of the leaves of the slot's block of kBoxBlock up to the slot
+    Box *suffix;        // [n] union from the slot to the end of its block
+    uint32_t *part;     // [kBoundsBlocks][12] partial bounds of the centroids and of the vertices
     int32_t *header;    // [16] [0] n, [1] kBvhMagic once a BUILD of n faces has
-                        // finished, [2] set to 1 by a REFIT that found no such BUILD
+                        // finished, [2] set to 1 by a REFIT that found no such BUILD;
+                        // [4..6] origin and [8..10] step of the nodes' boxes (floats)
 };
+constexpr int kBoundsBlocks = 256;
+constexpr int kBoxBlock = 256;
 
 // Seal of a built BVH buffer (header[1]); refit and traversal check it
 // together with header[0] == face count before they follow any stored index.

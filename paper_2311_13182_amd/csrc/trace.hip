@@ -78,37 +78,56 @@ __device__ __forceinline__ Shear make_shear(float3 d) {
     return sh;
 }
 
+// ---- the stackless walk ------------------------------------------------------
+// What bounds the walk is the bytes per node that each lane gets back from L1
+// (64 bytes per clock and CU, whether or not lanes share a line): a node of 16
+// bytes instead of 32 halves them.  The box comes as 16-bit steps from the
+// mesh's origin, so per query the ray's slab constants are scaled once, t = q
+// (step / d) + (origin - o) / d, and a test is 6 conversions, 6 fused
+// multiply-adds and the minima and maxima.
+struct Slab {
+    float3 m, b;   // step / d, (origin - o) / d
+};
+// zero direction components are replaced by tiny values
+__device__ __forceinline__ Slab make_slab(float3 o, float3 d, float3 org, float3 step) {
+    float3 id;
+    id.x = 1.0f / (fabsf(d.x) > 1e-30f ? d.x : copysignf(1e-30f, d.x));
+    id.y = 1.0f / (fabsf(d.y) > 1e-30f ? d.y : copysignf(1e-30f, d.y));
+    id.z = 1.0f / (fabsf(d.z) > 1e-30f ? d.z : copysignf(1e-30f, d.z));
+    Slab s;
+    s.m = make_float3(step.x * id.x, step.y * id.y, step.z * id.z);
+    s.b = make_float3((org.x - o.x) * id.x, (org.y - o.y) * id.y, (org.z - o.z) * id.z);
+    return s;
+}
+__device__ __forceinline__ bool box_hit(const BvhNode &nd, const Slab &s, float tlim) {
+    const float tx0 = fmaf((float)(nd.x & 0xffffu), s.m.x, s.b.x), tx1 = fmaf((float)(nd.x >> 16), s.m.x, s.b.x);
+    const float ty0 = fmaf((float)(nd.y & 0xffffu), s.m.y, s.b.y), ty1 = fmaf((float)(nd.y >> 16), s.m.y, s.b.y);
+    const float tz0 = fmaf((float)(nd.z & 0xffffu), s.m.z, s.b.z), tz1 = fmaf((float)(nd.z >> 16), s.m.z, s.b.z);
+    const float tn = fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fmaxf(fminf(tz0, tz1), 0.0f));
+    float tf = fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), fmaxf(tz0, tz1));
+    tf *= 1.0000005f;
+    return tn <= tf && tn <= tlim;
+}
+
 // Any hit of a triangle other than `self` at t in (tmin, tmax) along the unit
 // direction s from x: the occlusion test of a return segment.  Same stackless
 // walk as the closest-hit query, leaving at the first accepted hit.
 __device__ bool any_hit(const TraceArgs &a, int n_nodes, float3 x, float3 s, float tmin, float tmax, int self) {
     const Shear sh = make_shear(s);
-    float3 id;
-    id.x = 1.0f / (fabsf(s.x) > 1e-30f ? s.x : copysignf(1e-30f, s.x));
-    id.y = 1.0f / (fabsf(s.y) > 1e-30f ? s.y : copysignf(1e-30f, s.y));
-    id.z = 1.0f / (fabsf(s.z) > 1e-30f ? s.z : copysignf(1e-30f, s.z));
-    const float3 oid = make_float3(x.x * id.x, x.y * id.y, x.z * id.z);
+    const float *h = reinterpret_cast<const float *>(a.header);
+    const Slab sl = make_slab(x, s, make_float3(h[4], h[5], h[6]), make_float3(h[8], h[9], h[10]));
     int i = 0;
     while (i < n_nodes) {
         const BvhNode nd = a.nodes[i];
-        float tx0 = fmaf(nd.lo[0], id.x, -oid.x), tx1 = fmaf(nd.hi[0], id.x, -oid.x);
-        float ty0 = fmaf(nd.lo[1], id.y, -oid.y), ty1 = fmaf(nd.hi[1], id.y, -oid.y);
-        float tz0 = fmaf(nd.lo[2], id.z, -oid.z), tz1 = fmaf(nd.hi[2], id.z, -oid.z);
-        float tn = fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fmaxf(fminf(tz0, tz1), 0.0f));
-        float tf = fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), fmaxf(tz0, tz1));
-        tf *= 1.0000005f;
-        const bool hit = tn <= tf && tn <= tmax;
-        const int esc = nd.escape > i ? nd.escape : i + 1;
-        if (!hit) {
-            i = esc;
+        const bool leaf = (nd.link & kLeafBit) != 0u;
+        if (!box_hit(nd, sl, tmax)) {
+            i = leaf ? i + 1 : max((int)nd.link, i + 1);
             continue;
         }
-        if (nd.leaf < 0) {
-            i++;
-            continue;
-        }
-        if (nd.leaf < a.n_tris) {
-            const LeafTri lt = a.tris[nd.leaf];
+        i++;
+        const uint32_t slot = nd.link & ~kLeafBit;
+        if (leaf && slot < (uint32_t)a.n_tris) {
+            const LeafTri lt = a.tris[slot];
             float th, c0, c1, c2;
             if (__float_as_int(lt.a.w) != self &&
                 wt_hit(sh, x, make_float3(lt.a.x, lt.a.y, lt.a.z), make_float3(lt.b.x, lt.b.y, lt.b.z),
@@ -116,7 +135,6 @@ __device__ bool any_hit(const TraceArgs &a, int n_nodes, float3 x, float3 s, flo
                 th > tmin && th < tmax)
                 return true;
         }
-        i = esc;
     }
     return false;
 }
@@ -132,6 +150,12 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
     // a buffer that no BUILD for this face count has sealed is never walked:
     // every ray misses
     const int n_nodes = (a.n_nodes > 0 && a.header[1] == kBvhMagic && a.header[0] == a.n_tris) ? a.n_nodes : 0;
+    const float *hd = reinterpret_cast<const float *>(a.header);
+    float3 org = make_float3(0.f, 0.f, 0.f), step = org;   // frame of the nodes' boxes
+    if (n_nodes > 0) {
+        org = make_float3(hd[4], hd[5], hd[6]);
+        step = make_float3(hd[8], hd[9], hd[10]);
+    }
     unsigned long long n_q = 0, n_node = 0, n_tri = 0;
     if (active) {
         const size_t R = (size_t)a.g.nx * a.g.ny;
@@ -163,13 +187,7 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
             n_q++;
             // per-ray shear constants of the watertight test
             const Shear sh = make_shear(d);
-            // slab-test reciprocals (zero components replaced by tiny values)
-            float3 id;
-            id.x = 1.0f / (fabsf(d.x) > 1e-30f ? d.x : copysignf(1e-30f, d.x));
-            id.y = 1.0f / (fabsf(d.y) > 1e-30f ? d.y : copysignf(1e-30f, d.y));
-            id.z = 1.0f / (fabsf(d.z) > 1e-30f ? d.z : copysignf(1e-30f, d.z));
-            float3 oid = make_float3(o.x * id.x, o.y * id.y, o.z * id.z);
-
+            const Slab sl = make_slab(o, d, org, step);
             int best = -1, bslot = -1;
             float t1 = INFINITY, t2 = INFINITY, bb0 = 0.f, bb1 = 0.f, bb2 = 0.f;
             float tlim = INFINITY;   // box cull limit: best t plus the tie margin
@@ -177,34 +195,19 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
             while (i < n_nodes) {
                 const BvhNode nd = a.nodes[i];
                 if (COUNT) n_node++;
-                float tx0 = fmaf(nd.lo[0], id.x, -oid.x), tx1 = fmaf(nd.hi[0], id.x, -oid.x);
-                float ty0 = fmaf(nd.lo[1], id.y, -oid.y), ty1 = fmaf(nd.hi[1], id.y, -oid.y);
-                float tz0 = fmaf(nd.lo[2], id.z, -oid.z), tz1 = fmaf(nd.hi[2], id.z, -oid.z);
-                float tn = fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fmaxf(fminf(tz0, tz1), 0.0f));
-                float tf = fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), fmaxf(tz0, tz1));
-                tf *= 1.0000005f;
-                bool hit = tn <= tf && tn <= tlim;
-                // escape links always point forward; the guard keeps the walk
-                // finite even for a corrupted buffer
-                const int esc = nd.escape > i ? nd.escape : i + 1;
-                if (!hit) {
-                    i = esc;
+                const bool leaf = (nd.link & kLeafBit) != 0u;
+                if (!box_hit(nd, sl, tlim)) {
+                    // escape links always point forward; the guard keeps the walk
+                    // finite even for a corrupted buffer
+                    i = leaf ? i + 1 : max((int)nd.link, i + 1);
                     continue;
                 }
-                if (nd.leaf < 0) {
-                    i++;
-                    continue;
-                }
-                if (nd.leaf >= a.n_tris) {
-                    i = esc;
-                    continue;
-                }
-                const LeafTri lt = a.tris[nd.leaf];
+                i++;   // left child, or a leaf's escape
+                const uint32_t slot = nd.link & ~kLeafBit;
+                if (!leaf || slot >= (uint32_t)a.n_tris) continue;
+                const LeafTri lt = a.tris[slot];
                 const int fid = __float_as_int(lt.a.w);
-                if ((unsigned)fid >= (unsigned)a.n_tris) {   // not a face of this mesh
-                    i = esc;
-                    continue;
-                }
+                if ((unsigned)fid >= (unsigned)a.n_tris) continue;   // not a face of this mesh
                 if (COUNT) n_tri++;
                 float th, c0, c1, c2;
                 if (fid != prev &&
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
                         t2 = t1;
                         t1 = th;
                         best = fid;
-                        bslot = nd.leaf;
+                        bslot = (int)slot;
                         bb0 = c0;
                         bb1 = c1;
                         bb2 = c2;
@@ -224,7 +227,6 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
                         t2 = th;
                     }
                 }
-                i = esc;
             }
             if (best < 0) {
                 alive = false;
