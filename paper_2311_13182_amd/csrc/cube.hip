@@ -409,37 +409,62 @@ __global__ __launch_bounds__(256) void k_angle(const float2 *y, float2 *out, int
 
 // Conjugate transpose of the angle stage: out[v][e] = sum_a
 // e^{+2 pi j (a v mod Na) / Na} y[a][e] for every v < V, twiddles by exact
-// index from an LDS table; one thread per cell.
-template <int VB>
-__global__ __launch_bounds__(256) void k_angle_adj(const float2 *y, float2 *out, int V, int Na, long long CS) {
-    extern __shared__ float2 tw[];
-    for (int k = threadIdx.x; k < Na; k += blockDim.x) {
+// index from an LDS table.  A block takes 64 cells (a lane each) and splits the
+// angles over its kAngleAdjWaves wavefronts, whose sums are added in wave order
+// through LDS: with one thread per cell walking all angles a cube of 128 x 256
+// cells filled 128 CUs with 4 waves each and took 56 us at 64 angles; what is
+// left to bound it is reading the angle planes (16.8 MB there).
+// EXACT instances have V = VB; the other guards each antenna by the
+// wave-uniform test v < V.
+constexpr int kAngleAdjWaves = 8;
+
+template <int VB, bool EXACT>
+__global__ __launch_bounds__(64 * kAngleAdjWaves) void k_angle_adj(const float2 *y, float2 *out, int V, int Na,
+                                                                   long long CS) {
+    extern __shared__ float2 tw[];   // [Na], then [kAngleAdjWaves - 1][V][64] partial sums
+    float2 *part = tw + Na;
+    for (int k = threadIdx.x; k < Na; k += 64 * kAngleAdjWaves) {
         float sn, cs;
         sincospif(2.0f * (float)k / (float)Na, &sn, &cs);
         tw[k] = make_float2(cs, sn);
     }
     __syncthreads();
-    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (e >= CS) return;
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const long long e = (long long)blockIdx.x * 64 + lane;
+    const bool live = e < CS;
     float2 acc[VB];
 #pragma unroll
     for (int v = 0; v < VB; v++) acc[v] = make_float2(0.0f, 0.0f);
-    for (int a = 0; a < Na; a++) {
-        const float2 x = y[(size_t)a * CS + e];
-        int idx = 0;
+    if (live) {
+#pragma unroll 4
+        for (int a = g; a < Na; a += kAngleAdjWaves) {
+            const float2 x = y[(size_t)a * CS + e];
+            int idx = 0;
 #pragma unroll
-        for (int v = 0; v < VB; v++) {
-            if (v >= V) continue;
-            const float2 w = tw[idx];
-            acc[v].x = fmaf(w.x, x.x, fmaf(-w.y, x.y, acc[v].x));
-            acc[v].y = fmaf(w.x, x.y, fmaf(w.y, x.x, acc[v].y));
-            idx += a;
-            if (idx >= Na) idx -= Na;
+            for (int v = 0; v < VB; v++) {
+                if (!EXACT && v >= V) continue;
+                const float2 w = tw[idx];
+                acc[v].x = fmaf(w.x, x.x, fmaf(-w.y, x.y, acc[v].x));
+                acc[v].y = fmaf(w.x, x.y, fmaf(w.y, x.x, acc[v].y));
+                idx += a;
+                if (idx >= Na) idx -= Na;
+            }
         }
     }
+    if (g > 0) {
 #pragma unroll
-    for (int v = 0; v < VB; v++)
-        if (v < V) out[(size_t)v * CS + e] = acc[v];
+        for (int v = 0; v < VB; v++)
+            if (EXACT || v < V) part[((g - 1) * V + v) * 64 + lane] = acc[v];
+    }
+    __syncthreads();
+    if (g == 0) {
+#pragma unroll
+        for (int v = 0; v < VB; v++) {
+            if (!EXACT && v >= V) continue;
+            for (int q = 0; q < kAngleAdjWaves - 1; q++) acc[v] = cadd2(acc[v], part[(q * V + v) * 64 + lane]);
+            if (live) out[(size_t)v * CS + e] = acc[v];
+        }
+    }
 }
 
 // ---- Forward range FFT + angle DFT, fused (256 samples) -------------------
@@ -697,7 +722,11 @@ static size_t range_angle_lds(int V) {
 // ties).  The angle range is split over kPowSplit block rows and 4 lanes per
 // cell, so a cube with thousands of angle bins (planar arrays) still fills
 // the chip; partials are combined in a fixed order.
+// Up to kPowDirect angles one block row sums them all and writes the map itself
+// (64 angles: 16 loads per thread; the partials of 16 rows took as long to
+// write and combine as the cube to read).
 constexpr int kPowSplit = 16;
+constexpr int kPowDirect = 128;
 
 __global__ __launch_bounds__(256) void k_power_part(const float2 *X, int Na, int plane, float *psum, float *pmax,
                                                     int *parg) {
@@ -705,11 +734,12 @@ __global__ __launch_bounds__(256) void k_power_part(const float2 *X, int Na, int
     __shared__ int sa[4][64];
     const int cl = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int e = blockIdx.x * 64 + cl;
-    const int per = (Na + kPowSplit - 1) / kPowSplit;
+    const int per = (Na + (int)gridDim.y - 1) / (int)gridDim.y;
     const int a0 = blockIdx.y * per, a1 = min(Na, a0 + per);
     float acc = 0.0f, best = -1.0f;
     int ba = a0;
     if (e < plane) {
+#pragma unroll 4
         for (int a = a0 + g; a < a1; a += 4) {
             const float2 x = X[(size_t)a * plane + e];
             const float q = x.x * x.x + x.y * x.y;
@@ -735,7 +765,7 @@ __global__ __launch_bounds__(256) void k_power_part(const float2 *X, int Na, int
             }
         }
         psum[(size_t)blockIdx.y * plane + e] = sum;
-        pmax[(size_t)blockIdx.y * plane + e] = m;
+        if (pmax) pmax[(size_t)blockIdx.y * plane + e] = m;   // NULL: one block row, no combination
         parg[(size_t)blockIdx.y * plane + e] = am;
     }
 }
@@ -784,25 +814,97 @@ __global__ void k_cfar_cells(const float *P, int C, int S, int guard, int train,
     ratio[e] = rt;
 }
 
-// ordered compaction of detections (ratio > 1), one block
-__global__ __launch_bounds__(1024) void k_cfar_compact(const float *ratio, const int *am, int n, int S,
-                                                       int32_t *points, float *pratio, int maxp,
-                                                       int32_t *npts) {
-    __shared__ int wsum[16];
-    __shared__ int base;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (t == 0) base = 0;
+// The same for windows of up to kCfarWin cells either way: a block's tile of
+// cells with its border in LDS, row sums of the whole window and of its two
+// sides beside the guard cells first, then the column sums of those (the guard
+// cells are left out, not subtracted), in FP64; 42 additions per cell instead
+// of 441 loads (2 + 8 cells either way), and alpha, which depends on the range
+// bin only, once per column.
+constexpr int kCfarWin = 16;
+constexpr int kCfarTr = 64, kCfarTd = 4;   // tile: range bins x Doppler bins
+
+__global__ __launch_bounds__(256) void k_cfar_tile(const float *P, int C, int S, int guard, int train, double pfa,
+                                                   float *ratio) {
+    __shared__ float p[kCfarTd + 2 * kCfarWin][kCfarTr + 2 * kCfarWin];
+    __shared__ double full[kCfarTd + 2 * kCfarWin][kCfarTr], side[kCfarTd + 2 * kCfarWin][kCfarTr];
+    __shared__ double scale[kCfarTr];   // alpha / nt
+    const int tr = (S + kCfarTr - 1) / kCfarTr;
+    const int r0 = (int)(blockIdx.x % tr) * kCfarTr, d0 = (int)(blockIdx.x / tr) * kCfarTd;
+    const int w = guard + train, rows = kCfarTd + 2 * w, cols = kCfarTr + 2 * w;
+    for (int i = threadIdx.x; i < rows * cols; i += 256) {
+        const int y = i / cols, x = i - y * cols;
+        const int d = ((d0 + y - w) % C + C) % C, r = r0 + x - w;
+        p[y][x] = r >= 0 && r < S ? P[(size_t)d * S + r] : 0.0f;
+    }
+    if (threadIdx.x < kCfarTr) {
+        const int r = r0 + (int)threadIdx.x;
+        const int nf = min(r + w, S - 1) - max(r - w, 0) + 1, ng = min(r + guard, S - 1) - max(r - guard, 0) + 1;
+        const int nt = r < S ? (2 * w + 1) * nf - (2 * guard + 1) * ng : 0;
+        scale[threadIdx.x] = nt > 0 ? pow(pfa, -1.0 / nt) - 1.0 : -1.0;   // alpha / nt; no cells: -1
+    }
     __syncthreads();
-    for (int e0 = 0; e0 < n; e0 += 1024) {
-        int e = e0 + t;
-        int hit = (e < n && ratio[e] > 1.0f) ? 1 : 0;
-        uint64_t m = __ballot(hit);
-        int before = __popcll(m & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+    for (int i = threadIdx.x; i < rows * kCfarTr; i += 256) {
+        const int y = i / kCfarTr, x = i - y * kCfarTr;
+        double sd = 0.0, mid = 0.0;
+        for (int q = 0; q < train; q++) sd += (double)p[y][x + q] + (double)p[y][x + 2 * w - q];
+        for (int q = train; q <= train + 2 * guard; q++) mid += p[y][x + q];
+        side[y][x] = sd;
+        full[y][x] = sd + mid;
+    }
+    __syncthreads();
+    const int x = threadIdx.x % kCfarTr, y = threadIdx.x / kCfarTr, r = r0 + x, d = d0 + y;
+    if (r >= S || d >= C) return;
+    double sum = 0.0;
+    for (int q = 0; q < train; q++) sum += full[y + q][x] + full[y + 2 * w - q][x];
+    for (int q = train; q <= train + 2 * guard; q++) sum += side[y + q][x];
+    float rt = 0.0f;
+    if (scale[x] >= 0.0) {
+        const double thr = scale[x] * sum;
+        const float pc = p[y + w][x + w];
+        rt = thr > 0.0 ? (float)((double)pc / thr) : (pc > 0.0f ? INFINITY : 0.0f);
+    }
+    ratio[(size_t)d * S + r] = rt;
+}
+
+// Ordered compaction of detections (ratio > 1): block b owns the cells [b per,
+// (b + 1) per), a multiple of 256; k_cfar_count leaves their number in cnt[b],
+// k_cfar_write sums the counts before its own and writes the block's points.
+constexpr int kCfarBlocks = 256;
+
+__device__ __forceinline__ int cfar_per(int n) { return (n + kCfarBlocks * 256 - 1) / (kCfarBlocks * 256) * 256; }
+
+__global__ __launch_bounds__(256) void k_cfar_count(const float *ratio, int n, int *cnt) {
+    __shared__ int sh[4];
+    const int per = cfar_per(n), e1 = min(n, ((int)blockIdx.x + 1) * per);
+    int c = 0;
+    for (int e = (int)blockIdx.x * per + (int)threadIdx.x; e < e1; e += 256) c += ratio[e] > 1.0f;
+    for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
+}
+
+__global__ __launch_bounds__(256) void k_cfar_write(const float *ratio, const int *am, const int *cnt, int n, int S,
+                                                    int32_t *points, float *pratio, int maxp, int32_t *npts) {
+    __shared__ int sh[4], wsum[4];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int mine = cnt[t];   // kCfarBlocks = 256 counts
+    int before = t < (int)blockIdx.x ? mine : 0;
+    for (int off = 32; off >= 1; off >>= 1) before += __shfl_xor(before, off);
+    if (lane == 0) sh[w] = before;
+    __syncthreads();
+    int base = sh[0] + sh[1] + sh[2] + sh[3];
+    if (blockIdx.x == kCfarBlocks - 1 && t == kCfarBlocks - 1) *npts = base + mine;
+    const int per = cfar_per(n), e1 = min(n, ((int)blockIdx.x + 1) * per);
+    for (int e0 = (int)blockIdx.x * per; e0 < e1; e0 += 256) {   // block-uniform trip count
+        const int e = e0 + t;
+        const bool hit = e < e1 && ratio[e] > 1.0f;
+        const uint64_t m = __ballot(hit);
         if (lane == 0) wsum[w] = __popcll(m);
         __syncthreads();
-        int off = base;
-        for (int i = 0; i < w; i++) off += wsum[i];
-        int pos = off + before;
+        int pos = base + __popcll(m & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+        for (int i = 0; i < w; i++) pos += wsum[i];
+        base += wsum[0] + wsum[1] + wsum[2] + wsum[3];
         if (hit && pos < maxp) {
             points[4 * pos] = e % S;
             points[4 * pos + 1] = e / S;
@@ -811,14 +913,7 @@ __global__ __launch_bounds__(1024) void k_cfar_compact(const float *ratio, const
             if (pratio) pratio[pos] = ratio[e];
         }
         __syncthreads();
-        if (t == 0) {
-            int tot = 0;
-            for (int i = 0; i < 16; i++) tot += wsum[i];
-            base += tot;
-        }
-        __syncthreads();
     }
-    if (t == 0) *npts = base;
 }
 
 // Detections -> world points.  Range bin r: beat frequency r f_s / S = mu tau,
@@ -1068,7 +1163,7 @@ size_t cfar_scratch_bytes(int C, int S) {
     cv.take<float>((size_t)C * S);
     cv.take<int>((size_t)C * S);
     cv.take<float>((size_t)C * S);
-    cv.take<float>((size_t)kPowSplit * C * S);
+    cv.take<float>(std::max((size_t)kCfarBlocks, (size_t)kPowSplit * C * S));
     cv.take<float>((size_t)kPowSplit * C * S);
     cv.take<int>((size_t)kPowSplit * C * S);
     return align_up(cv.off, 256);
@@ -1162,6 +1257,18 @@ struct AngleFwd {
 };
 
 template <int VB, bool EXACT>
+struct AngleAdj {
+    static bool launch(dim3 grid, size_t lds, hipStream_t s, const float2 *in, float2 *out, int V, int Na,
+                       long long CS) {
+        if (lds > 65536 && hipFuncSetAttribute((const void *)k_angle_adj<VB, EXACT>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+            return false;
+        hipLaunchKernelGGL((k_angle_adj<VB, EXACT>), grid, dim3(64 * kAngleAdjWaves), lds, s, in, out, V, Na, CS);
+        return true;
+    }
+};
+
+template <int VB, bool EXACT>
 struct RangeAngle {
     static bool launch(dim3 grid, size_t lds, hipStream_t s, const float2 *in, float2 *out, int V, int C, int Na,
                        int window) {
@@ -1187,11 +1294,11 @@ static int launch_angle(const float2 *in, float2 *out, int V, int Na, long long 
         const dim3 grid(bx, (unsigned)((Na + kAngleGroup - 1) / kAngleGroup));
         (void)AngleDispatch<AngleFwd>::run(V, grid, 0, s, in, out, V, Na, CS);   // every count has an instance
     } else {
-        if (V <= 16)
-            hipLaunchKernelGGL(k_angle_adj<16>, dim3(bx), dim3(256), sizeof(float2) * Na, s, in, out, V, Na, CS);
-        else
-            hipLaunchKernelGGL(k_angle_adj<kAngleVMax>, dim3(bx), dim3(256), sizeof(float2) * Na, s, in, out, V,
-                               Na, CS);
+        const size_t lds = sizeof(float2) * (Na + (size_t)(kAngleAdjWaves - 1) * V * 64);
+        if (!AngleDispatch<AngleAdj>::run(V, dim3((unsigned)((CS + 63) / 64)), lds, s, in, out, V, Na, CS)) {
+            set_error("angle adjoint: %zu bytes of LDS refused", lds);
+            return SBR_E_HIP;
+        }
     }
     SBR_LAUNCHED();
     return SBR_OK;
@@ -1291,16 +1398,28 @@ int cfar_launch(const float2 *cube, int Na, int C, int S, int guard, int train, 
     float *P = cv.take<float>(plane);
     int *am = cv.take<int>(plane);
     float *ratio = cv.take<float>(plane);
-    float *psum = cv.take<float>((size_t)kPowSplit * plane);
+    float *psum = cv.take<float>(std::max((size_t)kCfarBlocks, (size_t)kPowSplit * plane));
     float *pmax = cv.take<float>((size_t)kPowSplit * plane);
     int *parg = cv.take<int>((size_t)kPowSplit * plane);
-    hipLaunchKernelGGL(k_power_part, dim3((plane + 63) / 64, kPowSplit), dim3(256), 0, s, cube, Na, plane, psum,
-                       pmax, parg);
-    hipLaunchKernelGGL(k_power_final, dim3((plane + 255) / 256), dim3(256), 0, s, plane, psum, pmax, parg, P, am);
-    hipLaunchKernelGGL(k_cfar_cells, dim3((plane + 255) / 256), dim3(256), 0, s, P, C, S, guard, train, pfa,
-                       ratio);
-    hipLaunchKernelGGL(k_cfar_compact, dim3(1), dim3(1024), 0, s, ratio, am, plane, S, points, ratio_out, maxp,
-                       npts);
+    // the first partial array is free once the map is final: 256 counts
+    int *cnt = reinterpret_cast<int *>(psum);
+    if (Na <= kPowDirect) {
+        hipLaunchKernelGGL(k_power_part, dim3((plane + 63) / 64, 1), dim3(256), 0, s, cube, Na, plane, P,
+                           (float *)nullptr, am);
+    } else {
+        hipLaunchKernelGGL(k_power_part, dim3((plane + 63) / 64, kPowSplit), dim3(256), 0, s, cube, Na, plane, psum,
+                           pmax, parg);
+        hipLaunchKernelGGL(k_power_final, dim3((plane + 255) / 256), dim3(256), 0, s, plane, psum, pmax, parg, P, am);
+    }
+    if (guard + train <= kCfarWin)
+        hipLaunchKernelGGL(k_cfar_tile, dim3((unsigned)((S + kCfarTr - 1) / kCfarTr * ((C + kCfarTd - 1) / kCfarTd))),
+                           dim3(256), 0, s, P, C, S, guard, train, pfa, ratio);
+    else
+        hipLaunchKernelGGL(k_cfar_cells, dim3((plane + 255) / 256), dim3(256), 0, s, P, C, S, guard, train, pfa,
+                           ratio);
+    hipLaunchKernelGGL(k_cfar_count, dim3(kCfarBlocks), dim3(256), 0, s, ratio, plane, cnt);
+    hipLaunchKernelGGL(k_cfar_write, dim3(kCfarBlocks), dim3(256), 0, s, ratio, am, cnt, plane, S, points, ratio_out,
+                       maxp, npts);
     SBR_LAUNCHED();
     return SBR_OK;
 }
