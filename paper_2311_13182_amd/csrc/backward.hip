@@ -861,22 +861,63 @@ __global__ __launch_bounds__(kNodeThreads) void k_synth_adj_node(const AdjArgs *
     }
 }
 
-__global__ void k_reduce_abar(const int32_t *count, const float2 *part, const float *tpart, int nvs, int cap,
-                              float2 *abar, float *tdbar) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= count[0]) return;
-    float r = 0.0f, i = 0.0f, t = 0.0f;
-    for (int s = 0; s < nvs; s++) {
-        float2 x = part[(size_t)s * cap + p];
-        r += x.x;
-        i += x.y;
-        if (tpart) t += tpart[(size_t)s * cap + p];
+// For kSplitAntennas or more, per path: the partial sums of Abar (and
+// taudot_bar where tpart is given) of the nvs antenna groups in their order, and
+// the delay adjoints tau_bar[t n_rx + m] summed over m (rows 0 .. n_tx - 1) and
+// over t (rows n_tx ..), all that the geometry adjoint needs of them, written
+// over the path's column of tau_bar.  A block takes 64 paths, its wavefronts the
+// n_tx + n_rx + 1 sums in turn (at most kSumsPer each).  A ray's lane in the
+// geometry adjoint would walk the n_tx n_rx rows twice: 0.44 ms of it at 400
+// antennas, 0.07 ms here; at 12 antennas the lane's own sums are the cheaper
+// (0.15 ms where this kernel took 0.45 on the 2048^2-ray scene).
+constexpr int kSumsWaves = 8;
+constexpr int kSumsPer = (SBR_MAX_TX + SBR_MAX_RX + kSumsWaves) / kSumsWaves;
+
+__global__ __launch_bounds__(64 * kSumsWaves) void k_path_sums(const int32_t *count, const float2 *part,
+                                                               const float *tpart, int nvs, int cap, float2 *abar,
+                                                               float *tdbar, float *tau_bar, int ntx, int nrx) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int P = count[0];
+    if ((int)blockIdx.x * 64 >= P) return;   // uniform over the block
+    const int p = (int)blockIdx.x * 64 + lane;
+    const bool live = p < P;
+    const int n_out = ntx + nrx;
+    float out[kSumsPer];
+#pragma unroll
+    for (int i = 0; i < kSumsPer; i++) {
+        const int o = w + i * kSumsWaves;
+        float s = 0.0f;
+        if (live && o < n_out) {
+            const int n = o < ntx ? nrx : ntx, first = o < ntx ? o * nrx : o - ntx, step = o < ntx ? 1 : nrx;
+            const float *src = tau_bar + (size_t)first * cap + p;
+#pragma unroll 4
+            for (int q = 0; q < n; q++) s += src[(size_t)q * step * cap];
+        } else if (live && o == n_out) {
+            float r = 0.0f, im = 0.0f, t = 0.0f;
+#pragma unroll 4
+            for (int q = 0; q < nvs; q++) {
+                const float2 x = part[(size_t)q * cap + p];
+                r += x.x;
+                im += x.y;
+                if (tpart) t += tpart[(size_t)q * cap + p];
+            }
+            abar[p] = make_float2(r, im);
+            if (tpart) tdbar[p] = t;
+        }
+        out[i] = s;
     }
-    abar[p] = make_float2(r, i);
-    if (tpart) tdbar[p] = t;
+    __syncthreads();   // the columns have been read
+#pragma unroll
+    for (int i = 0; i < kSumsPer; i++) {
+        const int o = w + i * kSumsWaves;
+        if (live && o < n_out) tau_bar[(size_t)o * cap + p] = out[i];
+    }
 }
 
 constexpr int kParamSums = 16;
+
+// Blocks of the geometry adjoint from which on each takes several tiles of rays.
+constexpr int kGeomBlocks = 2048;
 
 struct GeomArgs {
     const float *verts;
@@ -890,12 +931,19 @@ struct GeomArgs {
     RadarDev rd;
     GridDev g;
     ChirpDev ch;
-    const int32_t *ray_first;
+    const int32_t *wave_first, *blk;   // path stage
     const uint8_t *flags;
     int32_t drop, exit_only;
+    // dL/dA: the sum of `parts` rows [cap]; dL/d taudot likewise, or NULL (no
+    // wanted gradient depends on it)
     const float2 *abar;
-    const float *tau_bar;   // [V][cap]
-    const float *tdbar;     // [cap] dL/d taudot, or NULL (no wanted gradient depends on it)
+    const float *tdbar;
+    int32_t parts;
+    // dL/dtau, rows of cap paths: TX t's leg takes the sum of the tx_n rows from
+    // t tx_n, RX m's leg that of the rx_n rows rx_first + m + i n_rx
+    const float *tau_bar;
+    int32_t tx_n, rx_n, rx_first;
+    int32_t tiles;          // tiles of 256 rays per block
     int32_t cap;
     float *grad;            // [nv][3]
     double *acc;            // [kParamSums + 2 n_mats] sums over rays: origin (3), velocity
@@ -917,21 +965,62 @@ __device__ __forceinline__ float3 cross3(float3 a, float3 b) {
 __device__ __forceinline__ float len3(float3 a) { return sqrtf(dot3(a, a)); }
 __device__ __forceinline__ float3 vload3(const float *v, int i) { return f3(v[3 * i], v[3 * i + 1], v[3 * i + 2]); }
 
-__device__ __forceinline__ void atomic_add3(float *g, int vi, float3 x) {
+// A block's vertex gradients, collected in LDS and added to global memory once
+// per block and vertex: the large faces of a scene are hit by every wavefront,
+// and atomics on the same few lines of memory are served one after another
+// (1.4 of 1.8 ms on the 2048^2-ray scene).  Open addressing over kVtxSlots
+// slots; a vertex that finds none in kVtxProbes goes to global memory.
+constexpr int kVtxSlots = 1024;
+constexpr int kVtxProbes = 4;
+
+struct VtxTable {
+    int key[kVtxSlots];
+    float g[kVtxSlots][3];
+};
+
+__device__ __forceinline__ void atomic_add3(VtxTable &tab, float *g, int vi, float3 x) {
+    float *dst = nullptr;
+    uint32_t slot = (uint32_t)vi * 2654435761u >> 22;   // 10 bits
+#pragma unroll
+    for (int i = 0; i < kVtxProbes; i++) {
+        if (!dst) {
+            int k = tab.key[slot];
+            if (k < 0) {
+                k = atomicCAS(&tab.key[slot], -1, vi);
+                if (k < 0) k = vi;
+            }
+            if (k == vi) dst = tab.g[slot];
+            slot = (slot + 1) & (kVtxSlots - 1);
+        }
+    }
+    if (dst) {
+        atomicAdd(&dst[0], x.x);
+        atomicAdd(&dst[1], x.y);
+        atomicAdd(&dst[2], x.z);
+        return;
+    }
     atomicAdd(&g[3 * vi], x.x);
     atomicAdd(&g[3 * vi + 1], x.y);
     atomicAdd(&g[3 * vi + 2], x.z);
 }
 
-// Sum of x over the run of consecutive lanes that share `key` (segmented
-// inclusive scan, lanes in order); valid in the last lane of each run.
-__device__ __forceinline__ float seg_sum(float x, int lane, int s0) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        float y = __shfl_up(x, off);
-        if (lane - off >= s0) x += y;
-    }
-    return x;
+// x of the lane N below in the same row of 16 lanes, 0 past the row's start.
+template <int N>
+__device__ __forceinline__ int row_up(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, 0x110 | N, 0xf, 0xf, true);   // row_shr:N
+}
+
+// Sum of x over the lanes of its row from the start of the run on (in[i]: the
+// lane 2^i below is in the run); complete in the last lane of the run.
+__device__ __forceinline__ float run_sum(float x, const bool (&in)[4]) {
+    float y = __int_as_float(row_up<1>(__float_as_int(x)));
+    x += in[0] ? y : 0.0f;
+    y = __int_as_float(row_up<2>(__float_as_int(x)));
+    x += in[1] ? y : 0.0f;
+    y = __int_as_float(row_up<4>(__float_as_int(x)));
+    x += in[2] ? y : 0.0f;
+    y = __int_as_float(row_up<8>(__float_as_int(x)));
+    return x + (in[3] ? y : 0.0f);
 }
 
 // Per ray: single-precision forward recompute of its bounces from the face
@@ -943,15 +1032,18 @@ __device__ __forceinline__ float seg_sum(float x, int lane, int s0) {
 // summed over runs of equal face ids first and added by one atomic per run.
 // The gradients summed over all rays (origin, velocity, rotation,
 // attenuation) are returned in sum[16] where wanted.
-template <int K>
-__device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const int lane, float (&sum)[kParamSums]) {
-    int first = 0, n = 0;               // n: bounces to recompute (last returning one + 1)
+template <int K, bool FULL>
+__device__ __forceinline__ void geom_ray(const GeomArgs &a, VtxTable &tab, const int r, const int lane,
+                                         float (&sum)[kParamSums]) {
+    int n = 0;                          // bounces to recompute (last returning one + 1)
     uint32_t mask = 0;                  // bounces that return a path
     if (r < a.R) {
-        first = a.ray_first[r];
         mask = ray_path_mask(a.tri, a.flags, (size_t)a.R, (size_t)r, a.g.K, a.nf, a.drop != 0, a.exit_only != 0, &n);
     }
     if (__ballot(n > 0) == 0) return;   // uniform over the wavefront
+    const int wave = __builtin_amdgcn_readfirstlane(r / kPathWave);
+    const int first = a.wave_first[wave] + a.blk[wave / (kPathBlock / kPathWave)];
+    int base = 0;                       // the wavefront's paths of earlier bounces
     const int ix = r % a.g.nx, iy = r / a.g.nx;
     double d0[3], dl[3], dwd;
     grid_dir_local(a.g, ix, iy, dl, &dwd);
@@ -959,10 +1051,13 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
     const float dw = (float)dwd;
     const float3 O = f3((float)a.rd.o[0], (float)a.rd.o[1], (float)a.rd.o[2]);
     // ---- forward recompute, cached per bounce
-    float3 X[K], D[K], VA[K], E1[K], E2[K];
+    float3 X[K], D[K];
     float T[K], CI[K], SG[K], LC[K];
     float2 RC[K], DRC[K], DEPS[K];
     int F[K], MAT[K];
+    // FULL = false: conductors only (r = -1 at every bounce, no derivatives) and
+    // no gradients but the vertices'
+    const bool fresnel = FULL && a.any_fresnel;
     float3 dir = f3((float)d0[0], (float)d0[1], (float)d0[2]);
     float3 o = O;
     float L = 0.0f;
@@ -984,9 +1079,6 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             const float dn = den / nl;
             X[k] = x;
             D[k] = dir;
-            VA[k] = va;
-            E1[k] = e1;
-            E2[k] = e2;
             T[k] = t;
             LC[k] = L;
             F[k] = f;
@@ -994,7 +1086,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             SG[k] = dn >= 0.0f ? 1.0f : -1.0f;
             cd rc = {-1.0, 0.0}, drc = {0.0, 0.0}, de = {0.0, 0.0};
             const int mi = a.mat_id ? (int)a.mat_id[f] : 0;
-            if (a.any_fresnel) {
+            if (fresnel) {
                 reflect_coef(a.mt, mi, a.ch.fc, (double)CI[k], rc, drc);
                 if (a.want_mats) de = reflect_deps(a.mt, mi, a.ch.fc, (double)CI[k]);
                 if (mi < a.mt.n && a.mt.mode[mi] != 0) MAT[k] = mi;
@@ -1016,7 +1108,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
     float gR[9];                            // dL/d rot from the antenna positions
 #pragma unroll
     for (int q = 0; q < 9; q++) gR[q] = 0.0f;
-    const bool want_rot = a.want_rot != 0;
+    const bool want_rot = FULL && a.want_rot != 0;
     float wJ = 0.0f;                        // sum over the ray's paths of Re(conj(Abar) A)
     const float atn = (float)a.rd.atten;
     float ga_atn = 0.0f;                    // dL/d attenuation
@@ -1039,13 +1131,20 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
     const float ic0 = (float)(1.0 / kC0);
 #pragma unroll
     for (int k = 0; k < K; k++) {
+        const int p = first + path_rank(mask, k, base);
         if ((mask >> k) & 1u) {
-            const int p = first + __popc(mask & ((1u << k) - 1u));
-            const float2 ab = a.abar[p];
-            float2 prod = make_float2(1.0f, 0.0f);
+            float2 ab = make_float2(0.f, 0.f);
+#pragma unroll 4
+            for (int i = 0; i < a.parts; i++) {
+                const float2 x = a.abar[(size_t)i * a.cap + p];
+                ab.x += x.x;
+                ab.y += x.y;
+            }
+            float2 prod = make_float2(k & 1 ? 1.0f : -1.0f, 0.0f);
+            if (FULL) prod = make_float2(1.0f, 0.0f);
 #pragma unroll
             for (int j = 0; j <= k; j++)
-                prod = make_float2(prod.x * RC[j].x - prod.y * RC[j].y, prod.x * RC[j].y + prod.y * RC[j].x);
+                if (FULL) prod = make_float2(prod.x * RC[j].x - prod.y * RC[j].y, prod.x * RC[j].y + prod.y * RC[j].x);
             const float3 qk = X[k] - O;
             const float Rk = len3(qk);
             const float qz = dot3(qk, ZB);
@@ -1068,7 +1167,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
                 gd0 = gd0 + (gk * ntg / ctx) * ZB;
                 gZ = gZ + (gk * ntg / ctx) * D0;
             }
-            if (a.any_fresnel) {
+            if (fresnel) {
 #pragma unroll
                 for (int j = 0; j <= k; j++) {
                     float2 ex = make_float2(sc * CI[k], 0.0f);
@@ -1099,14 +1198,10 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             }
             xb[k] = xb[k] + (Rb / Rk) * (X[k] - O);
             // the TX leg of antenna (t, m) moves with the sum over m of its
-            // delay adjoints, the RX leg with the sum over t; both sums are
-            // formed inside their loops (no runtime-indexed arrays)
+            // delay adjoints, the RX leg with the sum over t
             const float *tbp = a.tau_bar + p;
             float Tt = 0.0f;
-            for (int t = 0; t < ntx; t++) {
-                float ts = 0.0f;
-                for (int m = 0; m < nrx; m++) ts += tbp[(size_t)(t * nrx + m) * a.cap];
-                Tt += ts;
+            auto tx_leg = [&](int t, float ts) {
                 const float3 q = X[0] - f3((float)a.rd.tx[t][0], (float)a.rd.tx[t][1], (float)a.rd.tx[t][2]);
                 const float3 gq = (ts * ic0 / len3(q)) * q;
                 xb[0] = xb[0] + gq;
@@ -1119,10 +1214,8 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
                         gR[6 + c] -= gq.z * a.txl[t][c];
                     }
                 }
-            }
-            for (int m = 0; m < nrx; m++) {
-                float rs = 0.0f;
-                for (int t = 0; t < ntx; t++) rs += tbp[(size_t)(t * nrx + m) * a.cap];
+            };
+            auto rx_leg = [&](int m, float rs) {
                 const float3 q = X[k] - f3((float)a.rd.rx[m][0], (float)a.rd.rx[m][1], (float)a.rd.rx[m][2]);
                 const float3 gq = (rs * ic0 / len3(q)) * q;
                 xb[k] = xb[k] + gq;
@@ -1135,10 +1228,27 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
                         gR[6 + c] -= gq.z * a.rxl[m][c];
                     }
                 }
+            };
+            for (int t = 0; t < ntx; t++) {
+                float ts = 0.0f;
+#pragma unroll 4
+                for (int i = 0; i < a.tx_n; i++) ts += tbp[(size_t)(t * a.tx_n + i) * a.cap];
+                Tt += ts;
+                tx_leg(t, ts);
+            }
+            for (int m = 0; m < nrx; m++) {
+                float rs = 0.0f;
+#pragma unroll 4
+                for (int i = 0; i < a.rx_n; i++) rs += tbp[(size_t)(a.rx_first + m + i * nrx) * a.cap];
+                rx_leg(m, rs);
             }
             go = go - (Rb / Rk) * (X[k] - O);        // R_k = |x_k - origin|
             // taudot = 2 (u . d_1) / c
-            const float tdq = a.tdbar ? a.tdbar[p] * 2.0f * ic0 : 0.0f;
+            float tdq = 0.0f;
+            if (a.tdbar) {
+                for (int i = 0; i < a.parts; i++) tdq += a.tdbar[(size_t)i * a.cap + p];
+                tdq *= 2.0f * ic0;
+            }
             gu = gu + tdq * f3((float)d0[0], (float)d0[1], (float)d0[2]);
             gd0 = gd0 + tdq * U;
 #pragma unroll
@@ -1160,7 +1270,9 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             // Eqs. 6-7 with T attached to the first hit: x_0 = a + b1 e1 + b2 e2 at
             // fixed (b1, b2), d_0 = (x_0 - o) / |x_0 - o|, cell weight times
             // D / D_0 with D = |N . (x_0 - o)| / |x_0 - o|^3
-            const float3 e1 = E1[0], e2 = E2[0];
+            const float3 va = vload3(a.verts, a.faces[3 * F[0]]);
+            const float3 e1 = vload3(a.verts, a.faces[3 * F[0] + 1]) - va;
+            const float3 e2 = vload3(a.verts, a.faces[3 * F[0] + 2]) - va;
             const float3 N = cross3(e1, e2);
             const float nl = len3(N);
             const float3 nh = (1.0f / nl) * N;
@@ -1169,7 +1281,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             const float3 q = X[0] - O;
             const float r0 = len3(q);
             const float nn = dot3(N, N);
-            const float3 w0 = X[0] - VA[0];
+            const float3 w0 = X[0] - va;
             const float b1 = dot3(cross3(w0, e2), N) / nn, b2 = dot3(cross3(e1, w0), N) / nn;
             float3 db = (cib[0] * SG[0]) * nh + gd0;   // cos_0 = |d_0 . n|, Doppler 2 u.d_0 / c
             float3 nhb = (cib[0] * SG[0]) * d;
@@ -1189,7 +1301,9 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             dnext = f3(0.f, 0.f, 0.f);                  // d_0 no longer depends on the grid
             gd0 = f3(0.f, 0.f, 0.f);
         } else if (act) {
-            const float3 e1 = E1[j], e2 = E2[j];
+            const float3 va = vload3(a.verts, a.faces[3 * F[j]]);
+            const float3 e1 = vload3(a.verts, a.faces[3 * F[j] + 1]) - va;
+            const float3 e2 = vload3(a.verts, a.faces[3 * F[j] + 2]) - va;
             const float3 N = cross3(e1, e2);
             const float nl = len3(N);
             const float3 nh = (1.0f / nl) * N;
@@ -1206,7 +1320,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             nhb = nhb - 2.0f * (dn * dnext + ndn * d);
             const float den = dot3(N, d);           // t = N.(a - o) / (N.d)
             const float w = tbar / den;
-            float3 Nb = w * (VA[j] - X[j]);
+            float3 Nb = w * (va - X[j]);
             ga = w * N;
             ob = ob - w * N;
             db = db - (w * t) * N;
@@ -1218,24 +1332,29 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             else go = go + ob;                      // rays start at the origin
             dnext = db;
         }
-        // sum over runs of lanes that hit the same face, one atomic per run
+        // sum over runs of lanes of a 16-lane row that hit the same face (DPP moves:
+        // no LDS traffic), one addition to the table per run
         const int key = act ? F[j] : -1;
-        const int kprev = __shfl_up(key, 1);
-        int s0 = (lane == 0 || kprev != key) ? lane : 0;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) s0 = max(s0, __shfl_up(s0, off));
-        const int knext = __shfl_down(key, 1);
-        const bool tail = act && (lane == 63 || knext != key);
+        const int l16 = lane & 15;
+        const int kprev = row_up<1>(key);   // with all lanes active
+        int s0 = (l16 == 0 || kprev != key) ? l16 : 0;
+        s0 = max(s0, row_up<1>(s0));
+        s0 = max(s0, row_up<2>(s0));
+        s0 = max(s0, row_up<4>(s0));
+        s0 = max(s0, row_up<8>(s0));
+        const bool in[4] = {l16 - 1 >= s0, l16 - 2 >= s0, l16 - 4 >= s0, l16 - 8 >= s0};
+        const int knext = __builtin_amdgcn_update_dpp(0, key, 0x101, 0xf, 0xf, true);   // row_shl:1
+        const bool tail = act && (l16 == 15 || knext != key);
         float v9[9] = {ga.x, ga.y, ga.z, gb.x, gb.y, gb.z, gc.x, gc.y, gc.z};
 #pragma unroll
-        for (int q = 0; q < 9; q++) v9[q] = seg_sum(v9[q], lane, s0);
+        for (int q = 0; q < 9; q++) v9[q] = run_sum(v9[q], in);
         if (tail) {
             const int f = F[j];
-            atomic_add3(a.grad, a.faces[3 * f], f3(v9[0], v9[1], v9[2]));
-            atomic_add3(a.grad, a.faces[3 * f + 1], f3(v9[3], v9[4], v9[5]));
-            atomic_add3(a.grad, a.faces[3 * f + 2], f3(v9[6], v9[7], v9[8]));
+            atomic_add3(tab, a.grad, a.faces[3 * f], f3(v9[0], v9[1], v9[2]));
+            atomic_add3(tab, a.grad, a.faces[3 * f + 1], f3(v9[3], v9[4], v9[5]));
+            atomic_add3(tab, a.grad, a.faces[3 * f + 2], f3(v9[6], v9[7], v9[8]));
         }
-        if (a.want_mats) {
+        if (FULL && a.want_mats) {
             // one wavefront sum per distinct material of this bounce
             const int km = act ? MAT[j] : -1;
             uint64_t pending = __ballot(km >= 0);
@@ -1256,7 +1375,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
             }
         }
     }
-    if (a.acc) {
+    if (FULL && a.acc) {
         // d_0 = rot d_local: dL/drot += (dL/dd_0) d_local^T, where dL/dd_0 is
         // what the reverse sweep left for the first segment plus the Doppler part;
         // zb = rot e_z: the gains add dL/dzb to the third column
@@ -1271,29 +1390,49 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, const int r, const i
     }
 }
 
-// The sums over rays are taken in FP64 (wavefronts, the block, then one atomic
-// per block and sum into a.acc): they cancel, and in FP32 their value depended
-// on the order of the atomics at 1e-6.
-template <int K>
+// A block takes a.tiles consecutive tiles of 256 rays, so that its vertex table
+// holds what many wavefronts add to the same vertices.  The sums over rays are
+// taken in FP64 (wavefronts, the block, then one atomic per block and sum into
+// a.acc): they cancel, and in FP32 their value depended on the order of the
+// atomics at 1e-6.
+template <int K, bool FULL>
 __global__ __launch_bounds__(256) void k_geom_adj(GeomArgs a) {
+    __shared__ VtxTable tab;
     __shared__ double sh[4][kParamSums];
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    float sum[kParamSums];
-#pragma unroll
-    for (int q = 0; q < kParamSums; q++) sum[q] = 0.0f;
-    geom_ray<K>(a, r, lane, sum);
-    if (!a.acc) return;   // uniform over the grid
-#pragma unroll
-    for (int q = 0; q < kParamSums; q++) {
-        double d = (double)sum[q];
-        for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off);
-        if (lane == 0) sh[w][q] = d;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int i = tid; i < kVtxSlots; i += 256) {
+        tab.key[i] = -1;
+        tab.g[i][0] = tab.g[i][1] = tab.g[i][2] = 0.0f;
     }
     __syncthreads();
-    if (threadIdx.x < kParamSums)
-        atomicAdd(&a.acc[threadIdx.x],
-                  (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]));
+    const bool sums = FULL && a.acc;   // uniform over the grid
+    double acc = 0.0;
+    for (int i = 0; i < a.tiles; i++) {
+        const int tile = (int)blockIdx.x * a.tiles + i;
+        if (tile * 256LL >= a.R) break;
+        float sum[kParamSums];
+#pragma unroll
+        for (int q = 0; q < kParamSums; q++) sum[q] = 0.0f;
+        geom_ray<K, FULL>(a, tab, tile * 256 + tid, lane, sum);
+        if (!sums) continue;
+#pragma unroll
+        for (int q = 0; q < kParamSums; q++) {
+            double d = (double)sum[q];
+            for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off);
+            if (lane == 0) sh[w][q] = d;
+        }
+        __syncthreads();
+        if (tid < kParamSums) acc += (sh[0][tid] + sh[1][tid]) + (sh[2][tid] + sh[3][tid]);
+        __syncthreads();
+    }
+    if (sums && tid < kParamSums) atomicAdd(&a.acc[tid], acc);
+    __syncthreads();
+    for (int i = tid; i < kVtxSlots; i += 256) {
+        const int v = tab.key[i];
+        if (v < 0) continue;
+#pragma unroll
+        for (int c = 0; c < 3; c++) atomicAdd(&a.grad[3 * v + c], tab.g[i][c]);
+    }
 }
 
 // The parameter gradients wanted += the sums over rays.
@@ -1348,13 +1487,14 @@ struct BackExtra {
 static BackExtra back_extra(void *buf, int32_t R, int32_t K, int32_t V, int32_t C, int32_t S) {
     const long long cap = (long long)R * K;
     const BackPlan bp = back_plan(cap, V);
+    const bool sums = V >= kSplitAntennas;
     Carver cv(buf);
     BackExtra e;
     e.tau_bar = cv.take<float>((size_t)V * cap);
     e.part = cv.take<float2>((size_t)bp.nvs * cap);
-    e.abar = cv.take<float2>(cap);
+    e.abar = cv.take<float2>(sums ? cap : 0);
     e.tpart = cv.take<float>((size_t)bp.nvs * cap);
-    e.tdbar = cv.take<float>(cap);
+    e.tdbar = cv.take<float>(sums ? cap : 0);
     e.acc = cv.take<double>(kParamSums + 2 * SBR_MAX_MATERIALS);
     e.corr = nullptr;
     e.rows = nullptr;
@@ -1401,6 +1541,15 @@ size_t adj_table_bytes(int n) {
 // G rows per LDS stage of a request with S samples, with the 16-byte
 // work-item slot after them, within 64 KiB of LDS per block.
 static int adj_rows(int Sp) { return std::max(1, std::min<int>(kAdjRowsMax, (65536 - 16) / (int)(sizeof(float2) * Sp))); }
+
+template <int K = 1>
+static void launch_geom(const GeomArgs &g, dim3 grid, hipStream_t s) {
+    if constexpr (K < SBR_MAX_BOUNCES) {
+        if (g.g.K != K) return launch_geom<K + 1>(g, grid, s);
+    }
+    if (g.any_fresnel || g.acc) hipLaunchKernelGGL((k_geom_adj<K, true>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_geom_adj<K, false>), grid, dim3(256), 0, s, g);
+}
 
 int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream_t s) {
     if (n <= 0) return SBR_OK;
@@ -1483,13 +1632,20 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         g.rd = rd;
         g.g = q.gd;
         g.ch = q.cd;
-        g.ray_first = q.st.ray_first;
+        g.wave_first = q.st.wave_first;
+        g.blk = q.st.blk;
         g.flags = q.hits->flags;
         g.drop = (q.flags & SBR_DROP_FLAGGED) ? 1 : 0;
         g.exit_only = (q.flags & SBR_EXIT_ONLY) ? 1 : 0;
-        g.abar = e.abar;
+        const bool sums = V >= kSplitAntennas;   // k_path_sums
+        g.abar = sums ? e.abar : e.part;
+        g.tdbar = !td ? nullptr : sums ? e.tdbar : e.tpart;
+        g.parts = sums ? 1 : bp.nvs;
         g.tau_bar = e.tau_bar;
-        g.tdbar = td ? e.tdbar : nullptr;
+        g.tx_n = sums ? 1 : rd.n_rx;
+        g.rx_n = sums ? 1 : rd.n_tx;
+        g.rx_first = sums ? rd.n_tx : 0;
+        g.tiles = std::min(std::max(g.R / (256 * kGeomBlocks), 1), 16);
         g.cap = (int32_t)cap;
         g.grad = q.grad;
         const bool want = q.params && (q.params->materials || q.params->radar || q.params->rot || q.params->attenuation);
@@ -1597,22 +1753,16 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         const AdjArgs &a = aa[r];
         const GeomArgs &g = gg[r];
         const long long cap = a.rec.cap;
-        hipLaunchKernelGGL(k_reduce_abar, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, a.count, a.abar_part,
-                           g.tdbar ? a.tdb_part : nullptr, a.nvs, (int)cap, const_cast<float2 *>(g.abar),
-                           const_cast<float *>(g.tdbar));
-        SBR_LAUNCHED();
         if (g.R == 0 || g.nf == 0) continue;
-        dim3 gb((unsigned)((g.R + 255) / 256));
-        switch (g.g.K) {
-        case 1: hipLaunchKernelGGL(k_geom_adj<1>, gb, dim3(256), 0, s, g); break;
-        case 2: hipLaunchKernelGGL(k_geom_adj<2>, gb, dim3(256), 0, s, g); break;
-        case 3: hipLaunchKernelGGL(k_geom_adj<3>, gb, dim3(256), 0, s, g); break;
-        case 4: hipLaunchKernelGGL(k_geom_adj<4>, gb, dim3(256), 0, s, g); break;
-        case 5: hipLaunchKernelGGL(k_geom_adj<5>, gb, dim3(256), 0, s, g); break;
-        case 6: hipLaunchKernelGGL(k_geom_adj<6>, gb, dim3(256), 0, s, g); break;
-        case 7: hipLaunchKernelGGL(k_geom_adj<7>, gb, dim3(256), 0, s, g); break;
-        default: hipLaunchKernelGGL(k_geom_adj<8>, gb, dim3(256), 0, s, g); break;
+        if (a.V >= kSplitAntennas) {
+            hipLaunchKernelGGL(k_path_sums, dim3((unsigned)((cap + 63) / 64)), dim3(64 * kSumsWaves), 0, s, a.count,
+                               a.abar_part, g.tdbar ? a.tdb_part : nullptr, a.nvs, (int)cap,
+                               const_cast<float2 *>(g.abar), const_cast<float *>(g.tdbar), a.tau_bar, g.rd.n_tx,
+                               g.rd.n_rx);
+            SBR_LAUNCHED();
         }
+        dim3 gb((unsigned)((g.R + 256LL * g.tiles - 1) / (256LL * g.tiles)));
+        launch_geom(g, gb, s);
         if (g.acc) {
             const sbr_param_grads &pg = *reqs[order[r]].params;
             hipLaunchKernelGGL(k_param_add, dim3(1), dim3(256), 0, s, g.acc, g.mt.n, pg.materials, pg.radar, pg.rot,

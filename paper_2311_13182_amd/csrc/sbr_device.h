@@ -162,6 +162,16 @@ __device__ __forceinline__ uint32_t ray_path_mask(const int32_t *tri, const uint
 }
 
 
+// Index of the lane's path of bounce k among the wavefront's paths, `base` the
+// number of those of earlier bounces (updated); every lane calls it, in order
+// of k, with its own mask of returning bounces.
+__device__ __forceinline__ int path_rank(uint32_t mask, int k, int &base) {
+    const uint64_t b = __ballot((mask >> k) & 1u);
+    const int r = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+    base += __popcll(b);
+    return r;
+}
+
 // Deconvolution of the non-uniform FFT forms: 1 / Psi((s - S/2) / 2S) for
 // mode s < S, with Psi(xi) = int psi(z) e^{-2 pi j xi z} dz by the trapezoid
 // rule at kNuSteps points per grid unit (psi vanishes with all its

@@ -151,17 +151,27 @@ struct PathSoA {
     float *epsd;      // [cap] slope * tc * taudot / fs, cycles per sample per chirp
 };
 
-// Scratch layout of the path stage (compaction + records).
+// Scratch layout of the path stage (compaction + records).  Paths lie wavefront
+// by wavefront of kPathWave consecutive rays, bounce-major within one: the
+// wavefront's first returns in ray order, then its second ones, and so on.
+// Neighbouring paths then come from neighbouring rays at the same bounce, so a
+// wavefront of a kernel over rays meets a run of paths per bounce (coalesced),
+// and one of a kernel over paths meets similar beat frequencies.
 struct PathStage {
     int32_t *count;       // [0] = number of paths P, [1] = float bits of the largest
                           // max(|Re A|, |Im A|) over them
-    int32_t *ray_first;   // [R + 1] first path index of each ray
-    int32_t *blk;         // [nblk] per-block path counts then offsets
-    int32_t nblk;
+    int32_t *wave_first;  // [nwave] first path of each wavefront of rays, from its block's first
+    int32_t *blk;         // [nblk] first path of each block of kPathBlock rays
+    int32_t nwave, nblk;
     PathSoA rec;
 };
 
-constexpr int kPathBlock = 256;   // rays per block of the compaction kernels
+constexpr int kPathWave = 64;
+constexpr int kPathBlock = 1024;   // rays per block of the counting kernel
+
+// Antennas (TX times RX) from which on a path's delays are written, and their
+// adjoints summed, by kernels of their own rather than by the path's lane.
+constexpr int kSplitAntennas = 32;
 
 // Doppler nodes of the node form of the non-uniform FFT sums.  With nu =
 // fc t_chirp taudot (cycles per chirp) and kappa = slope / (fs fc), the phase

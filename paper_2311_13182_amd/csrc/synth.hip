@@ -32,39 +32,26 @@ __device__ __forceinline__ uint32_t ray_mask(const PathArgs &a, size_t r, int *n
     return ray_path_mask(a.tri, a.flags, (size_t)a.R, r, a.g.K, a.nf, a.drop != 0, a.exit_only != 0, nb);
 }
 
-__device__ __forceinline__ int block_sum(int x, int *sh) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-    if (lane == 0) sh[w] = x;
-    __syncthreads();
-    int t = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); i++) t += sh[i];
-    __syncthreads();
-    return t;
-}
-
-// inclusive prefix within the block (wave scan + wave offsets)
-__device__ __forceinline__ int block_incl_scan(int x, int *sh) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int off = 1; off < 64; off <<= 1) {
-        int y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) sh[w] = x;
-    __syncthreads();
-    int add = 0;
-    for (int i = 0; i < w; i++) add += sh[i];
-    __syncthreads();
-    return x + add;
-}
-
 __global__ __launch_bounds__(kPathBlock) void k_path_count(PathArgs a) {
     __shared__ int sh[kPathBlock / 64];
-    size_t r = (size_t)blockIdx.x * kPathBlock + threadIdx.x;
+    const size_t r = (size_t)blockIdx.x * kPathBlock + threadIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int nb;
     int n = r < (size_t)a.R ? __popc(ray_mask(a, r, &nb)) : 0;
-    int t = block_sum(n, sh);
-    if (threadIdx.x == 0) a.st.blk[blockIdx.x] = t;
+    for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+    if (lane == 0) sh[w] = n;
+    __syncthreads();
+    if (threadIdx.x < 64) {   // prefix over the block's 16 wavefronts
+        const int x = lane < kPathBlock / 64 ? sh[lane] : 0;
+        int incl = x;
+        for (int off = 1; off < kPathBlock / 64; off <<= 1) {
+            const int y = __shfl_up(incl, off);
+            if (lane >= off) incl += y;
+        }
+        const int wave = (int)blockIdx.x * (kPathBlock / 64) + lane;
+        if (lane < kPathBlock / 64 && wave < a.st.nwave) a.st.wave_first[wave] = incl - x;
+        if (lane == kPathBlock / 64 - 1) a.st.blk[blockIdx.x] = incl;
+    }
 }
 
 __global__ __launch_bounds__(1024) void k_path_scan(PathArgs a) {
@@ -91,7 +78,6 @@ __global__ __launch_bounds__(1024) void k_path_scan(PathArgs a) {
     if (t == 1023) {
         a.st.count[0] = part[1023];
         a.st.count[1] = 0;   // amplitude bound, raised by k_path_refine
-        a.st.ray_first[a.R] = part[1023];
     }
 }
 
@@ -111,11 +97,23 @@ __device__ __forceinline__ void block_raise(uint32_t m, uint32_t *bound, uint32_
 
 __device__ __forceinline__ double frac_d(double x) { return x - floor(x); }
 
-// Records of ray r's returning bounces (mask, the last one below nb) from
-// path p on; returns the bits of their largest max(|Re A|, |Im A|).
+// From this many antennas on the path stage leaves the hit points and the
+// middle length of a path (kPathGeom doubles, in the first rows of its own
+// columns of alpha and gamma) and k_path_antennas forms the delays.  A ray's
+// lane would take a square root and two stores per antenna and path while the
+// lanes whose rays miss wait: 234 us at 400 antennas, 23.5k paths of 524k
+// slots.  With 12 antennas the extra pass over the geometry costs more than
+// the waiting lanes.
+constexpr int kPathGeom = 7;
+
+// Records of ray r's returning bounces (mask, the last one below nb), its
+// wavefront's paths from `first` on; returns the bits of their largest max(|Re
+// A|, |Im A|).  All lanes of the wavefront call it (the path indices are
+// ranked by ballots per bounce).
 __device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r, const uint32_t mask, const int nb,
-                                               int p) {
+                                               const int first) {
     uint32_t amax = 0;
+    int base = 0;
     const int ix = (int)(r % a.g.nx), iy = (int)(r / a.g.nx);
     double d[3], dw;
     grid_ray(a.g, a.rd, ix, iy, d, &dw);
@@ -129,7 +127,9 @@ __device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r
     cd pr = {1.0, 0.0};
     const int cap = a.st.rec.cap;
     const int ntx = a.rd.n_tx, nrx = a.rd.n_rx;
-    for (int k = 0; k < nb; k++) {
+    for (int k = 0; k < a.g.K; k++) {
+        const int p = first + path_rank(mask, k, base);
+        if (k >= nb) continue;
         const int f = a.tri[(size_t)k * a.R + r];
         double va[3], vb[3], vc[3];
         for (int i = 0; i < 3; i++) {
@@ -182,6 +182,15 @@ __device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r
         a.st.rec.amp[p] = A;
         a.st.rec.beta[p] = (float)beta;
         a.st.rec.epsd[p] = (float)epsd;
+        if (ntx * nrx >= kSplitAntennas) {   // uniform: delays by k_path_antennas
+            const double q[kPathGeom] = {x1[0], x1[1], x1[2], x[0], x[1], x[2], Lmid};
+#pragma unroll
+            for (int i = 0; i < kPathGeom; i++) {
+                const uint64_t b = (uint64_t)__double_as_longlong(q[i]);
+                reinterpret_cast<uint32_t *>(a.st.rec.alpha)[(size_t)i * cap + p] = (uint32_t)b;
+                reinterpret_cast<uint32_t *>(a.st.rec.gamma)[(size_t)i * cap + p] = (uint32_t)(b >> 32);
+            }
+        } else
         // one square root per (TX, RX) pair instead of per-antenna distance
         // arrays: a runtime-indexed array would live in per-thread stack memory
         for (int t = 0; t < ntx; t++) {
@@ -198,7 +207,6 @@ __device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r
                 a.st.rec.gamma[(size_t)v * cap + p] = (float)(a.ch.slope * tau / a.ch.fs);
             }
         }
-        p++;
         for (int i = 0; i < 3; i++) {
             o[i] = x[i];
             xp[i] = x[i];
@@ -208,17 +216,56 @@ __device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r
     return amax;
 }
 
-__global__ __launch_bounds__(kPathBlock) void k_path_refine(PathArgs a) {
-    __shared__ int sh[kPathBlock / 64];
-    const size_t r = (size_t)blockIdx.x * kPathBlock + threadIdx.x;
-    const bool act = r < (size_t)a.R;
+constexpr int kRefineThreads = 256;
+
+__global__ __launch_bounds__(kRefineThreads) void k_path_refine(PathArgs a) {
+    __shared__ uint32_t sh[kRefineThreads / 64];
+    const size_t r = (size_t)blockIdx.x * kRefineThreads + threadIdx.x;
     int nb = 0;
-    const uint32_t mask = act ? ray_mask(a, r, &nb) : 0u;
-    const int n = __popc(mask);
-    const int p = a.st.blk[blockIdx.x] + block_incl_scan(n, sh) - n;
-    if (act) a.st.ray_first[r] = p;
-    const uint32_t amax = n > 0 ? refine_ray(a, r, mask, nb, p) : 0u;
-    block_raise(amax, reinterpret_cast<uint32_t *>(a.st.count) + 1, reinterpret_cast<uint32_t *>(sh));
+    const uint32_t mask = r < (size_t)a.R ? ray_mask(a, r, &nb) : 0u;
+    uint32_t amax = 0u;
+    if (__ballot(mask != 0u)) {   // uniform over the wavefront
+        const int wave = __builtin_amdgcn_readfirstlane((int)(r / kPathWave));
+        amax = refine_ray(a, r, mask, nb, a.st.wave_first[wave] + a.st.blk[wave / (kPathBlock / kPathWave)]);
+    }
+    block_raise(amax, reinterpret_cast<uint32_t *>(a.st.count) + 1, sh);
+}
+
+// alpha and gamma of all antennas for 64 paths a block: the RX distances once
+// per path (LDS), the TX ones by the wavefront that takes the TX's row of
+// antennas, coalesced stores along the paths.
+__global__ __launch_bounds__(512) void k_path_antennas(PathArgs a) {
+    __shared__ double geo[kPathGeom][64];
+    __shared__ double drx[SBR_MAX_RX][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int P = a.st.count[0];
+    if ((int)blockIdx.x * 64 >= P) return;   // uniform over the block
+    const int p = (int)blockIdx.x * 64 + lane, cap = a.st.rec.cap;
+    const bool live = p < P;
+    if (w < kPathGeom && live) {
+        const uint32_t lo = reinterpret_cast<const uint32_t *>(a.st.rec.alpha)[(size_t)w * cap + p];
+        const uint32_t hi = reinterpret_cast<const uint32_t *>(a.st.rec.gamma)[(size_t)w * cap + p];
+        geo[w][lane] = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    }
+    __syncthreads();   // read before the rows are written
+    const double x1[3] = {geo[0][lane], geo[1][lane], geo[2][lane]};
+    const double x[3] = {geo[3][lane], geo[4][lane], geo[5][lane]}, Lmid = geo[6][lane];
+    auto dist = [](const double (&u)[3], const double *v) {
+        return sqrt((u[0] - v[0]) * (u[0] - v[0]) + (u[1] - v[1]) * (u[1] - v[1]) + (u[2] - v[2]) * (u[2] - v[2]));
+    };
+    const int ntx = a.rd.n_tx, nrx = a.rd.n_rx;
+    for (int m = w; m < nrx; m += 8) drx[m][lane] = dist(x, a.rd.rx[m]);
+    __syncthreads();
+    if (!live) return;
+    for (int t = w; t < ntx; t += 8) {
+        const double dtx = dist(x1, a.rd.tx[t]);
+        for (int m = 0; m < nrx; m++) {
+            const double tau = (dtx + Lmid + drx[m][lane]) / kC0;
+            const int v = t * nrx + m;
+            a.st.rec.alpha[(size_t)v * cap + p] = (float)frac_d(a.ch.fc * tau);
+            a.st.rec.gamma[(size_t)v * cap + p] = (float)(a.ch.slope * tau / a.ch.fs);
+        }
+    }
 }
 
 }  // namespace
@@ -227,7 +274,8 @@ PathStage carve_path_stage(Carver &cv, int32_t R, int32_t K, int32_t V) {
     PathStage st;
     st.nblk = (R + kPathBlock - 1) / kPathBlock;
     st.count = cv.take<int32_t>(64);
-    st.ray_first = cv.take<int32_t>((size_t)R + 1);
+    st.nwave = (R + kPathWave - 1) / kPathWave;
+    st.wave_first = cv.take<int32_t>(std::max(1, st.nwave));
     st.blk = cv.take<int32_t>(st.nblk);
     long long cap = (long long)R * K;
     st.rec.cap = (int32_t)cap;
@@ -260,7 +308,10 @@ int launch_paths(const sbr_mesh *m, const MatTable &mt, const RadarDev &rd, cons
     a.st = st;
     hipLaunchKernelGGL(k_path_count, dim3(st.nblk), dim3(kPathBlock), 0, s, a);
     hipLaunchKernelGGL(k_path_scan, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_path_refine, dim3(st.nblk), dim3(kPathBlock), 0, s, a);
+    hipLaunchKernelGGL(k_path_refine, dim3((unsigned)((a.R + kRefineThreads - 1) / kRefineThreads)),
+                       dim3(kRefineThreads), 0, s, a);
+    if (rd.n_tx * rd.n_rx >= kSplitAntennas)
+        hipLaunchKernelGGL(k_path_antennas, dim3((unsigned)((st.rec.cap + 63) / 64)), dim3(512), 0, s, a);
     SBR_LAUNCHED();
     return SBR_OK;
 }
