@@ -202,7 +202,7 @@ struct NodePlan {
 struct SynthPlan {
     int32_t L, SB, tiles_per_v, n_chunks;
     int32_t nu, cg;      // non-uniform FFT form (L = 0): chirps (nodes) per spreading block
-    int32_t q, dup;      // node form: nodes (0: chirp rows), copies of each row in LDS
+    int32_t q;           // node form: nodes (0: chirp rows)
 };
 
 // A pointer read from a device table is generic; marking it global lets the
@@ -248,7 +248,7 @@ struct SynthArgs {
     // node form (nd.q > 0): cg nodes per spreading block, ncg node groups, the
     // fixed-point bits below the largest amplitude, the transformed rows; the
     // grids are [n_chunks][V][q][re, im][nu_row_len(S)]
-    int32_t dup, bits;
+    int32_t bits;
     double2 *modes;      // [V][q][S] deconvolved modes of each node row
     NodePlan nd;
 };

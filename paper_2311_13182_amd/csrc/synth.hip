@@ -1027,28 +1027,62 @@ __global__ __launch_bounds__(256) void k_nu_synth_rows(const SynthArgs *__restri
 // so a path is spread into q rows of 2S points (q = 6 for the 2048^2-ray scene
 // at 1 m/s) instead of one row per chirp (128 there).
 // k_node_spread: block = (path chunk, antenna, group of cg nodes).  Real and
-// imaginary parts are separate 64-bit integer cells in LDS, contributions
-// rounded at 2^bits over the largest amplitude of the request (bits >= 31, 36
-// for that scene), so the sums are exact, in any order, without emptying the
-// cells on the way: nothing is held back for carries as in a packed word, and
-// the rounding (2^-36 of the largest amplitude) is far below single precision.
-// A product w_t (L_j A z) of two floats is exact in FP64; the fused add of
-// 1.5 2^52 rounds it to an integer held in the low mantissa bits.
-// What bounds it is the rate of 64-bit LDS atomics (14 q per path and
-// antenna), so the order of a lane's 7 q cells is chosen as in k_nu_spread: the
-// first cell of lane l lies on bank pair l mod 32 and additions to one cell
-// by one instruction stay rare.  Rows are RLs = 7 (mod 32) bank pairs apart,
-// so cell (row, j + t) is on bank pair 7 row + t + j; with e = (l - j) mod 32 a
-// lane starts at row e / 7 and tap e % 7 and walks the taps and then the nodes
-// cyclically.  With fewer than 5 nodes each row is held in `dup` copies, so
-// that the starting rows still differ between lanes.
-__device__ __forceinline__ int node_row_stride(int RL) { return RL + ((7 - RL) & 31); }
+// imaginary parts are separate 64-bit integer cells in LDS at 2^bits over the
+// largest amplitude of the request (bits >= 31, 36 for that scene), so sums over
+// wavefronts and blocks are exact, in any order, and nothing is held back for
+// carries as in a packed word.
+// A wavefront's 64 paths are neighbours on the surface they come from, so their
+// first cells differ little: each half of them is summed in windows of 16 cells
+// by the matrix cores, cells x 2q values = (7 weights placed in 16 zeros)^T
+// (amplitude times L_j), paths contracted four to an instruction, and one
+// addition per cell and value goes to LDS where each path made 14 q.  Windows
+// start at the smallest first cell left, so every path is in exactly one; a
+// wavefront of scattered paths takes more of them.  The products of a window
+// (two single-precision factors each) are summed in single precision, at most
+// 32 at a time.
+// One addition per path, cell and value to LDS took 3.87 ms at 2048^2 rays, 12
+// antennas and 256 samples (7.4M paths, q = 7): half of it the integer
+// conversions, the walk that spread the lanes over the banks, and the rest the
+// atomics.  This takes 1.62 ms: 3.2 half windows per 64 paths and antenna,
+// bound by vector instructions (about 400) and matrix ones (16, 35 clocks
+// each), which single-precision MFMA does not overlap.  In FP64 MFMA (70
+// clocks) it took 2.09 ms.
+__host__ __device__ inline int node_row_stride(int RL) { return RL + 16 + ((4 - RL) & 7); }
 
-__global__ __launch_bounds__(1024) void k_node_spread(const SynthArgs *__restrict__ args,
-                                                      const int32_t *__restrict__ didx,
-                                                      const int32_t *__restrict__ first, int m) {
+constexpr int kNodeSpreadThreads = 1024;
+constexpr int kNodeStage = 20;   // words per staged row of 16: rows start on 16 banks
+constexpr int kWin = 16, kWinSpan = kWin - kNuW;   // cells of a window, spread of first taps within it
+
+// LDS of a spreading block with `cg` nodes: the rows (16 cells longer than a
+// row, so that a window never passes the end; a lane's four rows of a window 16
+// bank pairs apart), then 32 staged rows of 16 words per wavefront.
+inline size_t node_spread_lds(int RL, int cg) {
+    return (size_t)16 * cg * node_row_stride(RL) + (size_t)2 * kNodeStage * kNodeSpreadThreads;
+}
+
+// Orders the wavefront's own LDS writes and reads (its lanes run in step).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Smallest x of the wavefront (all lanes active), by DPP moves.
+__device__ __forceinline__ int wave_min(int x) {
+    constexpr int big = 0x7fffffff;
+    x = min(x, __builtin_amdgcn_update_dpp(big, x, 0x111, 0xf, 0xf, false));   // row_shr:1, 2, 4, 8
+    x = min(x, __builtin_amdgcn_update_dpp(big, x, 0x112, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(big, x, 0x114, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(big, x, 0x118, 0xf, 0xf, false));
+    x = min(x, __builtin_amdgcn_update_dpp(big, x, 0x142, 0xa, 0xf, false));   // row_bcast:15
+    x = min(x, __builtin_amdgcn_update_dpp(big, x, 0x143, 0xc, 0xf, false));   // row_bcast:31
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
+__global__ __launch_bounds__(kNodeSpreadThreads) void k_node_spread(const SynthArgs *__restrict__ args,
+                                                                    const int32_t *__restrict__ didx,
+                                                                    const int32_t *__restrict__ first, int m) {
     extern __shared__ unsigned long long nsp[];
-    __shared__ float2 tab[kMaxNodes];
     const int j = nu_request(first, m, (int)blockIdx.x);
     const SynthArgs &a = args[didx[j]];
     const int blk = (int)blockIdx.x - first[j];
@@ -1056,9 +1090,8 @@ __global__ __launch_bounds__(1024) void k_node_spread(const SynthArgs *__restric
     const int gi = blk % a.ncg, rest = blk / a.ncg;
     const int v = rest % a.V, chunk = rest / a.V;
     const int q_lo = gi * a.cg, nq = min(a.cg, a.nd.q - q_lo);
-    const int rows = nq * a.dup, plane = rows * RLs, tid = (int)threadIdx.x;
-    for (int i = tid; i < 2 * plane; i += 1024) nsp[i] = 0ull;
-    if (tid < a.nd.q) tab[tid] = a.nd.node[tid];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < 2 * nq * RLs; i += kNodeSpreadThreads) nsp[i] = 0ull;
     __syncthreads();
     const int P = __builtin_amdgcn_readfirstlane(*gmem(a.count));
     const long long per = ((long long)P + a.n_chunks - 1) / a.n_chunks;
@@ -1072,65 +1105,118 @@ __global__ __launch_bounds__(1024) void k_node_spread(const SynthArgs *__restric
     const auto eps = gmem(a.rec.epsd);
     const double cb = (double)a.nd.cbar;
     const int Q = a.nd.q;
-    const int lane = tid & 63;
-    for (int p = p0 + tid; p < p1; p += 1024) {
-        const float alpha = al[p], gamma = ga[p], beta = bet[p], epsd = eps[p];
-        const F2 A = amp[p];
+    const int col = lane & 15, quad = lane >> 4;
+    float *stage = reinterpret_cast<float *>(nsp + 2 * nq * RLs) + wave * 32 * kNodeStage;
+    float *mine = stage + (lane & 31) * kNodeStage;
+    const float *theirs = stage + quad * kNodeStage + col;
+    float n_alpha = 0.f, n_gamma = 0.f, n_beta = 0.f, n_eps = 0.f;
+    F2 n_amp = {0.f, 0.f};
+    float2 nd[8];   // nodes of the tile: uniform; of weight 0 past the last one
+    auto load_nodes = [&](int n0) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            nd[k] = a.nd.node[q_lo + min(n0 + k, nq - 1)];
+            if (n0 + k >= nq) nd[k].y = 0.0f;
+        }
+    };
+    load_nodes(0);
+    // the lane's next path is loaded while the present one is spread
+    int pb = p0 + wave * 64;
+    if (pb < p1) {
+        const int p = min(pb + lane, p1 - 1);
+        n_alpha = al[p], n_gamma = ga[p], n_beta = bet[p], n_eps = eps[p], n_amp = amp[p];
+    }
+    for (; pb < p1; pb += kNodeSpreadThreads) {
+        const float alpha = n_alpha, gamma = n_gamma, beta = n_beta, epsd = n_eps;
+        const F2 A = n_amp;
+        {
+            const int p = min(pb + kNodeSpreadThreads + lane, p1 - 1);
+            n_alpha = al[p], n_gamma = ga[p], n_beta = bet[p], n_eps = eps[p], n_amp = amp[p];
+        }
         const NodePoint pt = node_point(alpha, (double)gamma, beta, epsd, cb, S);
         const double xr = rint(pt.x);
-        const int j0 = min(max((int)xr + S, 0), 2 * S);   // cell of the first tap xr - 3 (clamped: NaN-safe)
+        int j0 = min(max((int)xr + S, 0), 2 * S);   // cell of the first tap xr - 3 (clamped: NaN-safe)
         const float tau = node_offset(beta, a.nd.nu0f, a.nd.inv_h);   // [-1, 1]
-        float lp = 1.0f;
-        for (int k = 0; k < Q; k++) lp *= node_factor(tau, tab[k].x);
         const float wr = ldexpf(A.x * pt.zr - A.y * pt.zi, shift);
         const float wi = ldexpf(A.x * pt.zi + A.y * pt.zr, shift);
         float w[kNuW];
         nu_weights((float)(pt.x - xr), w);
-        const int e = (lane - j0) & 31;
-        int row = (e * 37) >> 8;        // e / 7
-        const int t0 = e - 7 * row;
-        row %= rows;
-        const int copy = row / nq;
-        int k = row - copy * nq;
-        // taps in the order t0, t0 + 1, ... (mod 7)
-        double wd[kNuW];
-        uint32_t off[kNuW];
-        {
-            float u[kNuW];
+        const bool live = pb + lane < p1;
+        if (!live) j0 = 1 << 30;
+        for (int n0 = 0; n0 < nq; n0 += 8) {   // tiles of 8 nodes
+            float f[8], lp = 1.0f;
 #pragma unroll
-            for (int t = 0; t < kNuW; t++) u[t] = (t0 & 1) ? w[(t + 1) % kNuW] : w[t];
-#pragma unroll
-            for (int t = 0; t < kNuW; t++) w[t] = (t0 & 2) ? u[(t + 2) % kNuW] : u[t];
-#pragma unroll
-            for (int t = 0; t < kNuW; t++) u[t] = (t0 & 4) ? w[(t + 4) % kNuW] : w[t];
-#pragma unroll
-            for (int t = 0; t < kNuW; t++) {
-                wd[t] = (double)u[t];
-                off[t] = (uint32_t)(t0 + t >= kNuW ? t0 + t - kNuW : t0 + t);
+            for (int k = 0; k < 8; k++) {
+                f[k] = node_factor(tau, nd[k].x);
+                lp *= n0 + k < nq ? f[k] : 1.0f;
             }
-        }
-        for (int i = 0; i < nq; i++) {
-            const float2 nd = tab[q_lo + k];
-            const float Lq = lp * nd.y * __builtin_amdgcn_rcpf(0.5f * node_factor(tau, nd.x));
-            const double br = (double)(wr * Lq), bi = (double)(wi * Lq);
-            unsigned long long *cell = nsp + (copy * nq + k) * RLs + j0;
-#pragma unroll
-            for (int t = 0; t < kNuW; t++) {
-                atomicAdd(cell + off[t], rint_word(br, wd[t]));
-                atomicAdd(cell + plane + off[t], rint_word(bi, wd[t]));
+            if (nq != Q || Q > 8) {   // uniform: nodes outside the tile
+                lp = 1.0f;
+                for (int k = 0; k < Q; k++) lp *= node_factor(tau, a.nd.node[k].x);
             }
-            k = k + 1 == nq ? 0 : k + 1;
+            float val[16];
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const float Lq = lp * nd[k].y * __builtin_amdgcn_rcpf(0.5f * f[k]);
+                val[2 * k] = wr * Lq;
+                val[2 * k + 1] = wi * Lq;
+            }
+            if (nq > 8) load_nodes(n0 + 8 < nq ? n0 + 8 : 0);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const bool here = (lane >> 5) == h;
+                uint64_t rem = __ballot(live && here);
+                if (!rem) continue;
+                float4 *row4 = reinterpret_cast<float4 *>(mine);
+                if (here) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++)
+                        row4[k] = make_float4(val[4 * k], val[4 * k + 1], val[4 * k + 2], val[4 * k + 3]);
+                }
+                wave_lds_fence();
+                float va[8];
+#pragma unroll
+                for (int g = 0; g < 8; g++) va[g] = theirs[4 * g * kNodeStage];
+                wave_lds_fence();
+                while (rem) {
+                    const int base = wave_min((rem >> lane) & 1 ? j0 : 0x7fffffff);
+                    const bool in = here && (uint32_t)(j0 - base) <= (uint32_t)kWinSpan;
+                    const uint64_t mem = __ballot(in);
+                    rem &= ~mem;
+                    if (here) {
+#pragma unroll
+                        for (int k = 0; k < 4; k++) row4[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
+                    if (in) {
+#pragma unroll
+                        for (int t = 0; t < kNuW; t++) mine[j0 - base + t] = w[t];
+                    }
+                    wave_lds_fence();
+                    const uint32_t mh = (uint32_t)(mem >> (32 * h));
+                    float vb[8];   // all reads in flight at once
+#pragma unroll
+                    for (int g = 0; g < 8; g++) vb[g] = theirs[4 * g * kNodeStage];
+                    f32x4s acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int g = 0; g < 8; g++)
+                        if ((mh >> (4 * g)) & 15u)
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[g], vb[g], acc, 0, 0, 0);
+                    wave_lds_fence();
+                    // lane's sums: rows 4 quad + r of the tile, cell `col` of the window
+                    unsigned long long *dst = nsp + (2 * n0 + 4 * quad) * RLs + base + col;
+#pragma unroll
+                    for (int r = 0; r < 4; r++)
+                        if (2 * n0 + 4 * quad + r < 2 * nq) atomicAdd(dst + r * RLs, rint_word((double)acc[r], 1.0));
+                }
+            }
         }
     }
     __syncthreads();
     // the chunk's rows [q][re, im][RL] of request j's partial
     long long *dst = a.grid + (((size_t)chunk * a.V + v) * Q + q_lo) * (size_t)RL * 2;
-    for (int i = tid; i < nq * 2 * RL; i += 1024) {
-        const int r2 = i / RL, jj = i - r2 * RL;   // r2 = 2 node + (0: re, 1: im)
-        const unsigned long long *src = nsp + (r2 & 1) * plane + (r2 >> 1) * RLs + jj;
-        unsigned long long sum = 0ull;
-        for (int d = 0; d < a.dup; d++) sum += src[d * nq * RLs];
-        dst[i] = (long long)sum;
+    for (int i = tid; i < nq * 2 * RL; i += kNodeSpreadThreads) {
+        const int row = i / RL;   // 2 node + (0: re, 1: im)
+        dst[i] = (long long)nsp[row * RLs + i - row * RL];
     }
 }
 
@@ -1379,21 +1465,22 @@ NodePlan node_plan(const RadarDev &rd, const GridDev &g, const ChirpDev &ch) {
     return n;
 }
 
-// Node form: as many node rows per spreading block as 160 KiB of LDS hold (two
-// blocks then share a CU at 256 samples), path chunks for about two blocks
-// per CU, of at least 8192 path slots.  Its grids and transformed rows fit the
-// words that the chirp-row plan of the same sizes asks for (2 q <= C).
+// Node form: as many node rows per spreading block as 160 KiB of LDS hold
+// beside the staged rows, path chunks (of at least 8192 path slots) for at most
+// two blocks per CU, whole rounds of the one block that a CU holds: 516 blocks
+// of the 2048^2-ray scene took 3.06 ms where 504 took 2.22.  Below 8M path
+// slots one round: its rows are half as many to sum (recon, 3M slots: rows 26 ->
+// 18 us, spreading the same).  Its grids and transformed rows fit the words that
+// the chirp-row plan of the same sizes asks for (2 q <= C).
 SynthPlan synth_node_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S, int32_t q) {
     SynthPlan p{};
     p.nu = 1;
     p.q = q;
     const int RL = nu_row_len(S);
-    const long long row_bytes = 16LL * (RL + ((7 - RL) & 31));
-    const int fit = (int)std::max(1LL, (nu_lds_budget() - 1024) / row_bytes);
-    p.cg = std::min(q, fit);
-    p.dup = std::max(1, std::min((5 + p.cg - 1) / p.cg, fit / p.cg));
+    const long long stage = (long long)node_spread_lds(RL, 0), row = (long long)node_spread_lds(RL, 1) - stage;
+    p.cg = (int32_t)std::max(1LL, std::min<long long>(q, (nu_lds_budget() - 1024 - stage) / row));
     const long long ncg = (q + p.cg - 1) / p.cg, cap = (long long)R * K;
-    const long long want = (512 + (long long)V * ncg - 1) / ((long long)V * ncg);
+    const long long want = std::max(1LL, (cap >= (8LL << 20) ? 512 : 256) / ((long long)V * ncg));
     const long long words = (long long)synth_grid_words(nu_plan(R, K, V, C, S), V, C, S);
     const long long rows = 2LL * V * q * RL, modes = 2LL * V * q * S + 2;
     p.n_chunks = (int32_t)std::max(1LL, std::min({want, (cap + 8191) / 8192, (words - modes) / rows}));
@@ -1457,7 +1544,6 @@ SynthArgs synth_args(const PathStage &st, const SynthPlan &p, const NodePlan &nd
     a.amax = amax;
     if (p.q) {
         a.nd = nd;
-        a.dup = p.dup;
         // a row's sum over all path slots stays below 2^62 (|A psi L| < 2^(bits + 1))
         int lg = 0;
         while ((1LL << lg) < (long long)st.rec.cap) lg++;
@@ -1556,7 +1642,7 @@ int launch_synth_batch(const SynthArgs *args, const int *L, int n, void *table, 
             add(h.dfirst, mk, (long long)a.n_chunks * a.V * a.ncg);
             add(h.drows, mk, (long long)a.V * a.nd.q);
             add(h.dchirps, mk++, (rows * a.S + 255) / 256);
-            lds_nspread = std::max(lds_nspread, (size_t)16 * a.cg * a.dup * (RL + ((7 - RL) & 31)));
+            lds_nspread = std::max(lds_nspread, node_spread_lds(RL, a.cg));
             lds_nrows = std::max(lds_nrows, (size_t)2 * 2 * a.S * sizeof(double2));
         } else {
             if ((long long)a.cg * (nu_row_len(a.S) + 1) > (long long)kNuCells * kNuSpreadThreads) {
@@ -1609,7 +1695,7 @@ int launch_synth_batch(const SynthArgs *args, const int *L, int n, void *table, 
                                         (int)lds_nspread));
         {
             ProfScope pk(kProfNuSpread, s);
-            hipLaunchKernelGGL(k_node_spread, dim3((unsigned)h.dfirst[mk]), dim3(1024), lds_nspread, s, t.args,
+            hipLaunchKernelGGL(k_node_spread, dim3((unsigned)h.dfirst[mk]), dim3(kNodeSpreadThreads), lds_nspread, s, t.args,
                                t.didx, t.dfirst, mk);
         }
         SBR_LAUNCHED();

@@ -65,3 +65,35 @@ def test_nodes_match_the_direct_sums(C, Sn, n_tx, n_rx, vel):
     for a, b, what in zip(*out, ("vertices", "vertices alone", "origin", "velocity", "rotation")):
         e = float((a - b).norm() / b.norm())
         assert e <= tol, f"{what}: {e:.2e}"
+
+
+@pytest.mark.parametrize("C,Sn,vel,spread", [(64, 256, (0, 0, 1), 9.0), (64, 256, (0, 0, 1), 0.5), (256, 128, (0, 0, 15), 9.0),
+                                             (8, 33, (0, 0, 0), 4.0)])
+def test_windows_of_scattered_ranges(C, Sn, vel, spread):
+    """Neighbouring rays that hit small plates at unrelated ranges: a wavefront's
+    paths fall into many windows of 16 cells (or, with 0.5 m, into a few)."""
+    import torch
+    from oracle import pyoracle as orc
+    from paper_2311_13182_amd.sbr import Simulator
+    rng = np.random.default_rng(5)
+    n = 400
+    c = np.stack([rng.uniform(-0.3, 0.3, n), rng.uniform(-0.3, 0.3, n), np.ones(n)], 1)
+    z = 1.0 + spread * rng.uniform(0, 1, n)
+    c *= z[:, None]
+    e = rng.normal(size=(n, 2, 3)) * (0.05 * z)[:, None, None] * (1, 1, 0.1)
+    v = np.concatenate([c, c + e[:, 0], c + e[:, 1]]).astype(np.float32)
+    f = np.stack([np.arange(n), np.arange(n) + n, np.arange(n) + 2 * n], 1).astype(np.int32)
+    sc = S.Scene("scattered", v, f, S.default_radar(1, 2, vel=vel), S.Chirp(n_samples=Sn, n_chirps=C),
+                 S.Grid(48, 41, 0.3, 0.3, 2))
+    tr = orc.trace(sc)
+    p = orc.paths(sc, tr["tri"], tr["flags"])
+    assert len(p["amp"]) > 400
+    sim = Simulator(sc)
+    sim.hits = device_hits_from_oracle(tr)
+    got = sim.synth()
+    assert torch.equal(got, sim.synth())
+    err = np.abs(torch.view_as_complex(got).cpu().numpy() - orc.synth(sc, p)).max() / np.abs(p["amp"]).sum()
+    gam = sc.chirp.slope / sc.chirp.fs * 2 * (2.0 + 2 * spread) / S.C0
+    tol = 3.6e-6 + 2 * np.pi * (Sn * gam + C) * 2.0 ** -25
+    log(f"scattered C={C} S={Sn} spread={spread}: {len(p['amp'])} paths, error {err:.2e} (tolerance {tol:.2e})")
+    assert err <= tol
