@@ -1,5 +1,8 @@
 // Ray launch + stackless BVH traversal + watertight ray-triangle test +
-// specular multi-bounce, one lane per ray, 8x8 ray tiles per wavefront.
+// specular multi-bounce, one lane per ray and 8x8 ray tiles per wavefront (small
+// grids: 16 lanes per ray, 2x2 tiles).
+#include <type_traits>
+
 #include "sbr_internal.h"
 #include "sbr_device.h"
 
@@ -79,12 +82,15 @@ __device__ __forceinline__ Shear make_shear(float3 d) {
 }
 
 // ---- the stackless walk ------------------------------------------------------
-// What bounds the walk is the bytes per node that each lane gets back from L1
-// (64 bytes per clock and CU, whether or not lanes share a line): a node of 16
-// bytes instead of 32 halves them.  The box comes as 16-bit steps from the
-// mesh's origin, so per query the ray's slab constants are scaled once, t = q
-// (step / d) + (origin - o) / d, and a test is 6 conversions, 6 fused
-// multiply-adds and the minima and maxima.
+// A node is 16 bytes (half of what its box takes in floats): it comes as 16-bit
+// steps from the mesh's origin, so per query the ray's slab constants are scaled
+// once, t = q (step / d) + (origin - o) / d, and a test is 6 conversions, 6 fused
+// multiply-adds and the minima and maxima, about 30 instructions.  What bounds a
+// large grid are these and the triangle tests of the few lanes at a leaf; a
+// small one the latency of the loads.  The next node is loaded as soon as it is
+// known, before a leaf's test, and the triangle in one piece: 20480 faces at
+// 512^2 rays and 3 bounces 230 -> 199 us, 200k at 1024^2 with occlusion 346 -> 281
+// us, 51200 at 2048^2 and 4 bounces 904 -> 868 us.
 struct Slab {
     float3 m, b;   // step / d, (origin - o) / d
 };
@@ -109,43 +115,120 @@ __device__ __forceinline__ bool box_hit(const BvhNode &nd, const Slab &s, float 
     return tn <= tf && tn <= tlim;
 }
 
+// ---- several lanes per ray ----------------------------------------------------
+// A grid of a few thousand rays is bound by the latency of the walk's steps (one
+// wavefront per SIMD or fewer, about 1000 clocks per node with a leaf's test
+// among the 64 lanes).  There L = 16 lanes take a ray: each walks a subtree, a
+// hit of one culls for all, and the hits are merged at the end, with the results
+// of the single walk.  The extra nodes (each lane's own way down, less culling)
+// make it slower once the chip is full: 14 faces at 64^2 rays 32.8 -> 18.3 us,
+// at 192^2 26.8 -> 22.0; 20000 faces at 64^2 84 -> 64 us, 128^2 80 -> 64, 160^2 79
+// -> 68, 192^2 81 -> 83, 256^2 78 -> 143; 1000 faces at 128^2 38.6 -> 38.5, 192^2
+// 41 -> 50.  The line is at 128^2.  (4 lanes: 28, 77 and 80 us at the first,
+// third and fourth of these.)
+constexpr long long kSplitRays = 128 * 128;
+constexpr int kSplitLanes = 16;
+
+// x of a lane of the other half of the 2 M lanes around, for M = 1, 2, 4, 8 in
+// turn: lanes of a half hold equal values by then, so that mirrors will do.
+template <int M>
+__device__ __forceinline__ int other_half(int x) {
+    constexpr int ctrl = M == 1 ? 0xb1     // quad_perm 1,0,3,2
+                         : M == 2 ? 0x4e   // quad_perm 2,3,0,1
+                         : M == 4 ? 0x141  // row_half_mirror
+                                  : 0x140; // row_mirror
+    return __builtin_amdgcn_update_dpp(x, x, ctrl, 0xf, 0xf, false);
+}
+template <int M>
+__device__ __forceinline__ float other_half(float x) {
+    return __int_as_float(other_half<M>(__float_as_int(x)));
+}
+// f<M>() for M = 1, 2, .. below L
+template <int L, int M = 1, class F>
+__device__ __forceinline__ void over_lanes(F &&f) {
+    if constexpr (M < L) {
+        f(std::integral_constant<int, M>{});
+        over_lanes<L, 2 * M>(f);
+    }
+}
+
+// The part of the depth-first node order that lane `sub` of L walks: the
+// subtrees L leaves of the top log2 L levels hold.  A leaf met on the way down
+// goes to the lowest of its lanes.
+template <int L>
+__device__ __forceinline__ void lane_range(const BvhNode *nodes, int n_nodes, int sub, int &first, int &last) {
+    first = 0;
+    last = n_nodes;
+#pragma unroll
+    for (int m = L / 2; m >= 1; m >>= 1) {
+        if (first >= last) break;
+        const uint32_t link = nodes[first].link;
+        if (link & kLeafBit) {
+            if (sub & (2 * m - 1)) last = first;
+            break;
+        }
+        const int left = first + 1;   // an inner node's children follow it
+        if (left >= last) break;
+        const uint32_t ll = nodes[left].link;
+        const int right = min((ll & kLeafBit) ? left + 1 : max((int)ll, left + 1), last);
+        if (sub & m) first = right;
+        else first = left, last = right;
+    }
+}
+
 // Any hit of a triangle other than `self` at t in (tmin, tmax) along the unit
 // direction s from x: the occlusion test of a return segment.  Same stackless
-// walk as the closest-hit query, leaving at the first accepted hit.
-__device__ bool any_hit(const TraceArgs &a, int n_nodes, float3 x, float3 s, float tmin, float tmax, int self) {
+// walk as the closest-hit query, leaving at the first accepted hit of the ray's
+// lanes.
+template <int L>
+__device__ bool any_hit(const TraceArgs &a, int first, int last, float3 x, float3 s, float tmin, float tmax, int self) {
     const Shear sh = make_shear(s);
     const float *h = reinterpret_cast<const float *>(a.header);
     const Slab sl = make_slab(x, s, make_float3(h[4], h[5], h[6]), make_float3(h[8], h[9], h[10]));
-    int i = 0;
-    while (i < n_nodes) {
-        const BvhNode nd = a.nodes[i];
+    int i = first;
+    bool hit = false;
+    BvhNode next = {};
+    if (i < last) next = a.nodes[i];
+    auto visit = [&]() {
+        const BvhNode nd = next;
         const bool leaf = (nd.link & kLeafBit) != 0u;
-        if (!box_hit(nd, sl, tmax)) {
-            i = leaf ? i + 1 : max((int)nd.link, i + 1);
-            continue;
-        }
-        i++;
+        const bool in = box_hit(nd, sl, tmax);
+        i = in || leaf ? i + 1 : max((int)nd.link, i + 1);
+        if (i < last) next = a.nodes[i];
         const uint32_t slot = nd.link & ~kLeafBit;
-        if (leaf && slot < (uint32_t)a.n_tris) {
+        if (in && leaf && slot < (uint32_t)a.n_tris) {
             const LeafTri lt = a.tris[slot];
             float th, c0, c1, c2;
-            if (__float_as_int(lt.a.w) != self &&
-                wt_hit(sh, x, make_float3(lt.a.x, lt.a.y, lt.a.z), make_float3(lt.b.x, lt.b.y, lt.b.z),
-                       make_float3(lt.c.x, lt.c.y, lt.c.z), th, c0, c1, c2) &&
-                th > tmin && th < tmax)
-                return true;
+            const bool on = wt_hit(sh, x, make_float3(lt.a.x, lt.a.y, lt.a.z), make_float3(lt.b.x, lt.b.y, lt.b.z),
+                                   make_float3(lt.c.x, lt.c.y, lt.c.z), th, c0, c1, c2);
+            if (on && __float_as_int(lt.a.w) != self && th > tmin && th < tmax) hit = true;
+        }
+    };
+    if (L == 1) {
+        while (i < last && !hit) visit();
+        return hit;
+    }
+    bool any = false;   // of the ray's lanes
+    while (__ballot(i < last && !any)) {
+        if (i < last && !any) visit();
+        if (__ballot(hit && !any)) {
+            int v = hit ? 1 : 0;
+            over_lanes<L>([&](auto m) { v |= other_half<decltype(m)::value>(v); });
+            any = v != 0;
         }
     }
-    return false;
+    return any;
 }
 
-template <bool COUNT, bool SHADOW>
+template <bool COUNT, bool SHADOW, int L>
 __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
     const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int tile = gid >> 6, l = gid & 63;
-    const int tiles_x = (a.g.nx + 7) >> 3;
-    const int ix = (tile % tiles_x) * 8 + (l & 7);
-    const int iy = (tile / tiles_x) * 8 + (l >> 3);
+    constexpr int W = L == 1 ? 8 : 2;   // W x W rays per wavefront
+    static_assert(W * W * L == 64, "lanes per ray");
+    const int tile = gid >> 6, sub = gid & (L - 1), l = (gid & 63) / L;
+    const int tiles_x = (a.g.nx + W - 1) / W;
+    const int ix = (tile % tiles_x) * W + l % W;
+    const int iy = (tile / tiles_x) * W + l / W;
     const bool active = ix < a.g.nx && iy < a.g.ny;
     // a buffer that no BUILD for this face count has sealed is never walked:
     // every ray misses
@@ -156,6 +239,9 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
         org = make_float3(hd[4], hd[5], hd[6]);
         step = make_float3(hd[8], hd[9], hd[10]);
     }
+    int first, last;
+    lane_range<L>(a.nodes, n_nodes, sub, first, last);
+    const bool lead = sub == 0;
     unsigned long long n_q = 0, n_node = 0, n_tri = 0;
     if (active) {
         const size_t R = (size_t)a.g.nx * a.g.ny;
@@ -177,43 +263,44 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
         for (int k = 0; k < a.g.K; k++) {
             const size_t slot = (size_t)k * R + r;
             if (!alive) {
-                a.tri[slot] = -1;
-                a.t[slot] = 0.0f;
-                a.u[slot] = 0.0f;
-                a.v[slot] = 0.0f;
-                a.flags[slot] = 0;
+                if (lead) {
+                    a.tri[slot] = -1;
+                    a.t[slot] = 0.0f;
+                    a.u[slot] = 0.0f;
+                    a.v[slot] = 0.0f;
+                    a.flags[slot] = 0;
+                }
                 continue;
             }
-            n_q++;
+            n_q += lead;
             // per-ray shear constants of the watertight test
             const Shear sh = make_shear(d);
             const Slab sl = make_slab(o, d, org, step);
             int best = -1, bslot = -1;
             float t1 = INFINITY, t2 = INFINITY, bb0 = 0.f, bb1 = 0.f, bb2 = 0.f;
             float tlim = INFINITY;   // box cull limit: best t plus the tie margin
-            int i = 0;
-            while (i < n_nodes) {
-                const BvhNode nd = a.nodes[i];
+            int i = first;
+            BvhNode next = {};
+            if (i < last) next = a.nodes[i];
+            auto visit = [&]() -> bool {   // whether a closer hit was found
+                const BvhNode nd = next;
                 if (COUNT) n_node++;
                 const bool leaf = (nd.link & kLeafBit) != 0u;
-                if (!box_hit(nd, sl, tlim)) {
-                    // escape links always point forward; the guard keeps the walk
-                    // finite even for a corrupted buffer
-                    i = leaf ? i + 1 : max((int)nd.link, i + 1);
-                    continue;
-                }
-                i++;   // left child, or a leaf's escape
+                const bool in = box_hit(nd, sl, tlim);
+                // left child, or the escape; escape links always point forward,
+                // and the guard keeps the walk finite even for a corrupted buffer
+                i = in || leaf ? i + 1 : max((int)nd.link, i + 1);
+                if (i < last) next = a.nodes[i];   // in flight during the leaf's test
                 const uint32_t slot = nd.link & ~kLeafBit;
-                if (!leaf || slot >= (uint32_t)a.n_tris) continue;
+                if (!in || !leaf || slot >= (uint32_t)a.n_tris) return false;
                 const LeafTri lt = a.tris[slot];
                 const int fid = __float_as_int(lt.a.w);
-                if ((unsigned)fid >= (unsigned)a.n_tris) continue;   // not a face of this mesh
                 if (COUNT) n_tri++;
                 float th, c0, c1, c2;
-                if (fid != prev &&
-                    wt_hit(sh, o, make_float3(lt.a.x, lt.a.y, lt.a.z), make_float3(lt.b.x, lt.b.y, lt.b.z),
-                           make_float3(lt.c.x, lt.c.y, lt.c.z), th, c0, c1, c2) &&
-                    th > tmin) {
+                const bool on = wt_hit(sh, o, make_float3(lt.a.x, lt.a.y, lt.a.z), make_float3(lt.b.x, lt.b.y, lt.b.z),
+                                       make_float3(lt.c.x, lt.c.y, lt.c.z), th, c0, c1, c2);
+                // fid: a face of this mesh, and not the one the ray starts on
+                if (on && th > tmin && fid != prev && (unsigned)fid < (unsigned)a.n_tris) {
                     if (th < t1 || (th == t1 && fid < best)) {
                         t2 = t1;
                         t1 = th;
@@ -222,19 +309,53 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
                         bb0 = c0;
                         bb1 = c1;
                         bb2 = c2;
-                        tlim = t1 + 1e-6f * fmaxf(1.0f, Lprev + t1);
-                    } else if (th < t2) {
-                        t2 = th;
+                        return true;
+                    }
+                    if (th < t2) t2 = th;
+                }
+                return false;
+            };
+            if (L == 1) {
+                while (i < last)
+                    if (visit()) tlim = t1 + 1e-6f * fmaxf(1.0f, Lprev + t1);
+            } else {
+                // lanes that are done stay, so that a hit of one culls for all
+                while (__ballot(i < last)) {
+                    bool closer = false;
+                    if (i < last) closer = visit();
+                    if (__ballot(closer)) {
+                        float t = t1;
+                        over_lanes<L>([&](auto m) { t = fminf(t, other_half<decltype(m)::value>(t)); });
+                        tlim = t + 1e-6f * fmaxf(1.0f, Lprev + t);
                     }
                 }
+                // the ray's closest hit (of equal ones the lowest face), and
+                // the second closest, of all its lanes
+                over_lanes<L>([&](auto m) {
+                    constexpr int M = decltype(m)::value;
+                    const float s1 = other_half<M>(t1), s2 = other_half<M>(t2), c0 = other_half<M>(bb0),
+                                c1 = other_half<M>(bb1), c2 = other_half<M>(bb2);
+                    const int sb = other_half<M>(best), ss = other_half<M>(bslot);
+                    t2 = fminf(fmaxf(t1, s1), fminf(t2, s2));
+                    if (s1 < t1 || (s1 == t1 && sb >= 0 && (best < 0 || sb < best))) {
+                        t1 = s1;
+                        best = sb;
+                        bslot = ss;
+                        bb0 = c0;
+                        bb1 = c1;
+                        bb2 = c2;
+                    }
+                });
             }
             if (best < 0) {
                 alive = false;
-                a.tri[slot] = -1;
-                a.t[slot] = 0.0f;
-                a.u[slot] = 0.0f;
-                a.v[slot] = 0.0f;
-                a.flags[slot] = 0;
+                if (lead) {
+                    a.tri[slot] = -1;
+                    a.t[slot] = 0.0f;
+                    a.u[slot] = 0.0f;
+                    a.v[slot] = 0.0f;
+                    a.flags[slot] = 0;
+                }
                 continue;
             }
             const LeafTri lt = a.tris[bslot];
@@ -270,13 +391,15 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
                 const float3 q = make_float3(o0.x - o.x, o0.y - o.y, o0.z - o.z);
                 const float D = sqrtf(q.x * q.x + q.y * q.y + q.z * q.z);
                 const float3 sd = make_float3(q.x / D, q.y / D, q.z / D);
-                if (any_hit(a, n_nodes, o, sd, tmin, D - tmin, best)) fl |= SBR_HIT_OCCLUDED;
+                if (any_hit<L>(a, first, last, o, sd, tmin, D - tmin, best)) fl |= SBR_HIT_OCCLUDED;
             }
-            a.tri[slot] = best;
-            a.t[slot] = t1;
-            a.u[slot] = bb1;
-            a.v[slot] = bb2;
-            a.flags[slot] = fl;
+            if (lead) {
+                a.tri[slot] = best;
+                a.t[slot] = t1;
+                a.u[slot] = bb1;
+                a.v[slot] = bb2;
+                a.flags[slot] = fl;
+            }
             d = make_float3(d.x - 2.0f * dn * nh.x, d.y - 2.0f * dn * nh.y, d.z - 2.0f * dn * nh.z);
             float dl = 1.0f / sqrtf(d.x * d.x + d.y * d.y + d.z * d.z);
             d = make_float3(d.x * dl, d.y * dl, d.z * dl);
@@ -303,6 +426,17 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a) {
 
 }  // namespace
 
+template <int L>
+static void launch_walk(const TraceArgs &a, bool shadow, hipStream_t st) {
+    constexpr int W = L == 1 ? 8 : 2;
+    const long long tiles = (long long)((a.g.nx + W - 1) / W) * ((a.g.ny + W - 1) / W);
+    const dim3 blocks((unsigned)((tiles + 3) / 4));
+    if (a.counters && shadow) hipLaunchKernelGGL((k_trace<true, true, L>), blocks, dim3(256), 0, st, a);
+    else if (a.counters) hipLaunchKernelGGL((k_trace<true, false, L>), blocks, dim3(256), 0, st, a);
+    else if (shadow) hipLaunchKernelGGL((k_trace<false, true, L>), blocks, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_trace<false, false, L>), blocks, dim3(256), 0, st, a);
+}
+
 int trace_launch(const sbr_mesh *m, const void *bvh, const RadarDev &rd, const GridDev &gd,
                  const sbr_hits *h, uint64_t *counters, hipStream_t st) {
     BvhView bv = bvh_view(const_cast<void *>(bvh), m->nf, nullptr);
@@ -321,21 +455,10 @@ int trace_launch(const sbr_mesh *m, const void *bvh, const RadarDev &rd, const G
     a.v = h->v;
     a.flags = h->flags;
     a.counters = reinterpret_cast<unsigned long long *>(counters);
-    long long tiles = (long long)((gd.nx + 7) / 8) * ((gd.ny + 7) / 8);
-    long long threads = tiles * 64;
-    int blocks = (int)((threads + 255) / 256);
-    {
-        ProfScope ps(kProfTrace, st);
-        const bool shadow = (gd.options & SBR_RAYS_SHADOW) != 0;
-        if (counters && shadow)
-            hipLaunchKernelGGL((k_trace<true, true>), dim3(blocks), dim3(256), 0, st, a);
-        else if (counters)
-            hipLaunchKernelGGL((k_trace<true, false>), dim3(blocks), dim3(256), 0, st, a);
-        else if (shadow)
-            hipLaunchKernelGGL((k_trace<false, true>), dim3(blocks), dim3(256), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_trace<false, false>), dim3(blocks), dim3(256), 0, st, a);
-    }
+    const bool shadow = (gd.options & SBR_RAYS_SHADOW) != 0;
+    ProfScope ps(kProfTrace, st);
+    if ((long long)gd.nx * gd.ny <= kSplitRays) launch_walk<kSplitLanes>(a, shadow, st);
+    else launch_walk<1>(a, shadow, st);
     SBR_LAUNCHED();
     return SBR_OK;
 }
