@@ -315,13 +315,7 @@ static int enqueue_synth(const sbr_mesh *mesh, const sbr_material *mats, int32_t
     const GridDev gd = make_grid(rays);
     const ChirpDev cd = make_chirp(chirp);
     NodePlan nd{};
-    if (synth_nu(S, flags)) nd = node_plan(rd, gd, cd);
-    // four chirps per node: 14 cells per node (real and imaginary parts apart)
-    // against 7 per chirp halve the LDS atomics.  Between two and four the gain
-    // was 1.8x at best (spreading 515 -> 282 us at 400 antennas x 16 chirps, 4
-    // nodes), and there few chirps average the chirp rows' fixed-point rounding,
-    // so the two forms' images differ by up to 3e-3 of their RMS
-    if (4 * nd.q >= C) nd.q = 0;
+    if (synth_nu(S, flags)) nd = synth_nodes(rd, gd, cd);
     if (nd.q) c.p = synth_node_plan(R, K, V, C, S, nd.q);
     int rc;
     if ((rc = launch_paths(mesh, make_mats(mats, n_mats), rd, gd, cd, hits, flags, c.st, s))) return rc;

@@ -932,6 +932,7 @@ struct GeomArgs {
     GridDev g;
     ChirpDev ch;
     const int32_t *wave_first, *blk;   // path stage
+    int32_t by_ray;                    // paths_by_ray
     const uint8_t *flags;
     int32_t drop, exit_only;
     // dL/dA: the sum of `parts` rows [cap]; dL/d taudot likewise, or NULL (no
@@ -1043,7 +1044,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, VtxTable &tab, const
     if (__ballot(n > 0) == 0) return;   // uniform over the wavefront
     const int wave = __builtin_amdgcn_readfirstlane(r / kPathWave);
     const int first = a.wave_first[wave] + a.blk[wave / (kPathBlock / kPathWave)];
-    int base = 0;                       // the wavefront's paths of earlier bounces
+    PathRank rank(mask, K, a.by_ray != 0);
     const int ix = r % a.g.nx, iy = r / a.g.nx;
     double d0[3], dl[3], dwd;
     grid_dir_local(a.g, ix, iy, dl, &dwd);
@@ -1131,7 +1132,7 @@ __device__ __forceinline__ void geom_ray(const GeomArgs &a, VtxTable &tab, const
     const float ic0 = (float)(1.0 / kC0);
 #pragma unroll
     for (int k = 0; k < K; k++) {
-        const int p = first + path_rank(mask, k, base);
+        const int p = first + rank.next(k);
         if ((mask >> k) & 1u) {
             float2 ab = make_float2(0.f, 0.f);
 #pragma unroll 4
@@ -1634,6 +1635,7 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         g.ch = q.cd;
         g.wave_first = q.st.wave_first;
         g.blk = q.st.blk;
+        g.by_ray = paths_by_ray(rd, q.gd, q.cd) ? 1 : 0;
         g.flags = q.hits->flags;
         g.drop = (q.flags & SBR_DROP_FLAGGED) ? 1 : 0;
         g.exit_only = (q.flags & SBR_EXIT_ONLY) ? 1 : 0;

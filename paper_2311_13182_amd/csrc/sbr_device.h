@@ -161,16 +161,29 @@ __device__ __forceinline__ uint32_t ray_path_mask(const int32_t *tri, const uint
     return mask;
 }
 
-
-// Index of the lane's path of bounce k among the wavefront's paths, `base` the
-// number of those of earlier bounces (updated); every lane calls it, in order
-// of k, with its own mask of returning bounces.
-__device__ __forceinline__ int path_rank(uint32_t mask, int k, int &base) {
-    const uint64_t b = __ballot((mask >> k) & 1u);
-    const int r = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-    base += __popcll(b);
-    return r;
-}
+// Index of the lane's path of bounce k among the wavefront's paths: bounce by
+// bounce, so that a bounce's records are contiguous, or ray by ray.  Every lane
+// constructs it with its own mask of returning bounces and calls next for k = 0,
+// 1, .. in turn.
+struct PathRank {
+    uint32_t mask;
+    int base;   // paths before the present bounce, or before the lane's ray
+    bool by_ray;
+    __device__ __forceinline__ static int below(uint64_t b) {   // set bits of lower lanes
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+    }
+    __device__ __forceinline__ PathRank(uint32_t mask, int K, bool by_ray) : mask(mask), base(0), by_ray(by_ray) {
+        if (by_ray)   // uniform
+            for (int k = 0; k < K; k++) base += below(__ballot((mask >> k) & 1u));
+    }
+    __device__ __forceinline__ int next(int k) {
+        if (by_ray) return base + __popc(mask & ((1u << k) - 1u));
+        const uint64_t b = __ballot((mask >> k) & 1u);
+        const int r = base + below(b);
+        base += __popcll(b);
+        return r;
+    }
+};
 
 // Deconvolution of the non-uniform FFT forms: 1 / Psi((s - S/2) / 2S) for
 // mode s < S, with Psi(xi) = int psi(z) e^{-2 pi j xi z} dz by the trapezoid

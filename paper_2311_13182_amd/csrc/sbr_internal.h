@@ -152,11 +152,17 @@ struct PathSoA {
 };
 
 // Scratch layout of the path stage (compaction + records).  Paths lie wavefront
-// by wavefront of kPathWave consecutive rays, bounce-major within one: the
-// wavefront's first returns in ray order, then its second ones, and so on.
-// Neighbouring paths then come from neighbouring rays at the same bounce, so a
-// wavefront of a kernel over rays meets a run of paths per bounce (coalesced),
-// and one of a kernel over paths meets similar beat frequencies.
+// by wavefront of kPathWave consecutive rays.  Within one, requests of the node
+// form have them bounce by bounce: the wavefront's first returns in ray order,
+// then its second ones, and so on.  Neighbouring paths then come from
+// neighbouring rays at the same bounce, so a wavefront of a kernel over rays
+// meets a run of paths per bounce (coalesced: path stage 0.57 -> 0.47 ms at 2048^2
+// rays), and one of a kernel over paths meets similar beat frequencies.  The
+// chirp rows' phase recurrences start at a chirp that depends on the lane, and
+// their contributions are rounded to 19 bits, so there the order of the paths
+// shows in the cube (5e-6, and 3e-3 of the RMS at the peaks of a 400-antenna
+// image): those requests have them ray by ray, and so have many antennas, where
+// kernels over paths do most of the work.
 struct PathStage {
     int32_t *count;       // [0] = number of paths P, [1] = float bits of the largest
                           // max(|Re A|, |Im A|) over them
@@ -256,6 +262,12 @@ struct SynthArgs {
 PathStage carve_path_stage(Carver &cv, int32_t R, int32_t K, int32_t V);
 // The Doppler nodes of a request; q = 0 where the chirp-row form is used.
 NodePlan node_plan(const RadarDev &rd, const GridDev &g, const ChirpDev &ch);
+// The synthesis' nodes: those of node_plan where it takes the node form, q = 0
+// where it takes chirp rows.
+NodePlan synth_nodes(const RadarDev &rd, const GridDev &g, const ChirpDev &ch);
+// Whether a request's paths lie ray by ray within a wavefront of rays (else
+// bounce by bounce); see PathStage.
+bool paths_by_ray(const RadarDev &rd, const GridDev &g, const ChirpDev &ch);
 SynthPlan synth_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S, bool nu);
 // The node form's plan: never more grid words than synth_plan(..., true) asks for.
 SynthPlan synth_node_plan(int32_t R, int32_t K, int32_t V, int32_t C, int32_t S, int32_t q);

@@ -26,6 +26,7 @@ struct PathArgs {
     GridDev g;
     ChirpDev ch;
     PathStage st;
+    int32_t by_ray;   // paths_by_ray
 };
 
 __device__ __forceinline__ uint32_t ray_mask(const PathArgs &a, size_t r, int *nb) {
@@ -113,7 +114,7 @@ constexpr int kPathGeom = 7;
 __device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r, const uint32_t mask, const int nb,
                                                const int first) {
     uint32_t amax = 0;
-    int base = 0;
+    PathRank rank(mask, a.g.K, a.by_ray != 0);
     const int ix = (int)(r % a.g.nx), iy = (int)(r / a.g.nx);
     double d[3], dw;
     grid_ray(a.g, a.rd, ix, iy, d, &dw);
@@ -128,7 +129,7 @@ __device__ __forceinline__ uint32_t refine_ray(const PathArgs &a, const size_t r
     const int cap = a.st.rec.cap;
     const int ntx = a.rd.n_tx, nrx = a.rd.n_rx;
     for (int k = 0; k < a.g.K; k++) {
-        const int p = first + path_rank(mask, k, base);
+        const int p = first + rank.next(k);
         if (k >= nb) continue;
         const int f = a.tri[(size_t)k * a.R + r];
         double va[3], vb[3], vc[3];
@@ -306,6 +307,7 @@ int launch_paths(const sbr_mesh *m, const MatTable &mt, const RadarDev &rd, cons
     a.g = gd;
     a.ch = cd;
     a.st = st;
+    a.by_ray = paths_by_ray(rd, a.g, a.ch) ? 1 : 0;
     hipLaunchKernelGGL(k_path_count, dim3(st.nblk), dim3(kPathBlock), 0, s, a);
     hipLaunchKernelGGL(k_path_scan, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(k_path_refine, dim3((unsigned)((a.R + kRefineThreads - 1) / kRefineThreads)),
@@ -1463,6 +1465,20 @@ NodePlan node_plan(const RadarDev &rd, const GridDev &g, const ChirpDev &ch) {
         n.node[k] = make_float2((float)std::cos(th), (float)((k & 1 ? -1.0 : 1.0) * std::sin(th) / (2.0 * q)));
     }
     return n;
+}
+
+// Four chirps per node: below that the node form's gain was 1.8x at best
+// (spreading 515 -> 282 us at 400 antennas x 16 chirps, 4 nodes), and there few
+// chirps average the chirp rows' fixed-point rounding, so the two forms' images
+// differ by up to 3e-3 of their RMS.
+NodePlan synth_nodes(const RadarDev &rd, const GridDev &g, const ChirpDev &ch) {
+    NodePlan n = node_plan(rd, g, ch);
+    if (4 * n.q >= ch.C) n.q = 0;
+    return n;
+}
+
+bool paths_by_ray(const RadarDev &rd, const GridDev &g, const ChirpDev &ch) {
+    return rd.n_tx * rd.n_rx >= kSplitAntennas || synth_nodes(rd, g, ch).q == 0;
 }
 
 // Node form: as many node rows per spreading block as 160 KiB of LDS hold
