@@ -25,12 +25,16 @@ PEAK_FP32_TFLOPS = 157.3      # MI355X published FP32 vector peak
 PEAK_HBM_GBS = 8000.0
 # LDS bandwidth from the unit counts: 256 CUs x 128 B per clock x 2.4 GHz
 PEAK_LDS_GBS = 256 * 128 * 2.4
-# the spreading of the non-uniform FFT synthesis: 7 taps, each one 64-bit LDS
-# atomic add of the packed (re, im) pair, per (path, antenna, chirp)
+# the spreading of the non-uniform FFT synthesis by chirp rows: 7 taps, each one
+# 64-bit LDS atomic add of the packed (re, im) pair, per (path, antenna, chirp)
 LDS_BYTES_PER_PAC = 7 * 8
-# the tap kernel of the non-uniform FFT adjoint: 7 float4 row reads from LDS
-# per (path, antenna, chirp)
+# the same by Doppler nodes: 7 taps times the real and imaginary parts of each
+# node's value, multiplied and added, per (path, antenna, node)
+FLOP_PER_PAN = 7 * 2 * 2
+# the tap kernels of the non-uniform FFT adjoint: float4 row reads from LDS, 7
+# per (path, antenna, chirp), or 8 per (path, antenna, node)
 LDS_READ_BYTES_PER_PAC = 7 * 16
+LDS_READ_BYTES_PER_PAN = 8 * 16
 FLOP_PER_PATH_SAMPLE = {"synth": 8.0, "synth_adj": 20.0}
 # lane operations per second of the FP32 vector units: 256 CUs x 4 SIMDs x 32
 # lanes x 2.4 GHz (one VALU instruction per lane per clock; an FMA counts once)
@@ -40,8 +44,27 @@ PEAK_VALU_LANE_OPS = 256 * 4 * 32 * 2.4e9
 OPS_PER_NODE_TEST, OPS_PER_TRI_TEST = 14, 27
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic__k_nu_spread__clutter_50k_fwd_bwd.md")
+def doppler_nodes(scene):
+    """Chebyshev nodes over the Doppler range of the ray grid that the library's
+    non-uniform FFT sums take (the fewest with an interpolation error of 1e-7 over
+    half the chirps' phases), 0 where it would take more than half the chirps."""
+    import math
+    import numpy as np
+    rd, ch, g = scene.radar, scene.chirp, scene.grid
+    u = np.asarray(rd.rot, dtype=np.float64).reshape(3, 3).T @ np.asarray(rd.vel, dtype=np.float64)
+    x, y = np.meshgrid(np.linspace(-g.tan_hx, g.tan_hx, 801), np.linspace(-g.tan_hy, g.tan_hy, 801))
+    f = (u[0] * x + u[1] * y + u[2]) / np.sqrt(1.0 + x * x + y * y)
+    h = 2.0 * ch.fc * ch.t_chirp / 299792458.0 * 0.5 * float(f.max() - f.min())
+    kappa = ch.slope / (ch.fs * ch.fc)
+    t = 2.0 * math.pi * (ch.n_chirps // 2) * max(1.0, abs(1.0 + (ch.n_samples - 1) * kappa)) * h
+    q = next((q for q in range(1, 33) if 4 * sum((0.5 * t) ** k / math.factorial(k) for k in range(q, q + 64)) <= 1e-7),
+             33)
+    return q if q <= 32 and 2 * q <= ch.n_chirps and 16 <= ch.n_samples <= 1024 else 0
+
+
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic__k_node_spread__clutter_50k_fwd_bwd.md")
 KERNEL_SOURCES = {
+    "k_node_spread": ["synth.hip", "sbr_internal.h", "sbr_device.h", "nu_weights.h"],
     "k_nu_spread": ["synth.hip", "sbr_internal.h", "sbr_device.h", "nu_weights.h"],
     "k_synth_adj_nu": ["backward.hip", "sbr_internal.h", "sbr_device.h", "nu_weights.h"],
     "k_synth_adj": ["backward.hip", "sbr_internal.h", "sbr_device.h"],
@@ -248,8 +271,21 @@ def main():
         k_ms[name] = tot / max(n, 1)
     ps = float(n_paths) * V * C * Sn          # path-samples per launch
     pac = float(n_paths) * V * C              # (path, antenna, chirp) per launch
+    pan = float(n_paths) * V                  # (path, antenna) per launch
     nufft = 16 <= Sn <= 1024                  # both sums run as non-uniform FFTs
-    if nufft:
+    q = doppler_nodes(scene)                  # rows per antenna of the node form, 0: one row per chirp
+    synth_q = q if 4 * q < C else 0           # the synthesis takes it from four chirps per node on
+    taps_bytes = LDS_READ_BYTES_PER_PAN * pan * q if q else LDS_READ_BYTES_PER_PAC * pac
+    if synth_q:
+        # the spreading kernel of the synthesis by Doppler nodes: the products of
+        # taps and node values on the matrix cores against the FP32 peak (windows
+        # of 16 cells hold 7 taps, 16 columns hold 2 q values, and the vector work
+        # that forms weights, phases and values does not overlap with them)
+        achieved = FLOP_PER_PAN * pan * synth_q / (k_ms["nu_spread"] * 1e-3) / 1e12
+        roof = {"bound": "alu", "kernel": "k_node_spread", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
+                "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
+                "traffic": measured_traffic("k_node_spread", args.workload)}
+    elif nufft:
         # the spreading kernel of the synthesis, bound by its 64-bit LDS atomics:
         # their operand bytes against the LDS bandwidth of the unit counts
         achieved = LDS_BYTES_PER_PAC * pac / (k_ms["nu_spread"] * 1e-3) / 1e9
@@ -296,19 +332,20 @@ def main():
         # both sums of the path-sample work run as non-uniform FFTs for 16 <= S <= 1024:
         # times per stage and the rates of the direct sums they replace (which a
         # direct evaluation could reach at most at the FP32 peak)
-        "synth": {"form": "nufft" if nufft else "direct", "ms": round(k_ms["synth"], 4),
+        "synth": {"form": "nufft" if nufft else "direct", "doppler_nodes": synth_q, "ms": round(k_ms["synth"], 4),
                   "spread_ms": round(k_ms["nu_spread"], 4) if nufft else None,
                   "direct_sum_equivalent_tflops": round(FLOP_PER_PATH_SAMPLE["synth"] * ps /
                                                         (k_ms["synth"] * 1e-3) / 1e12, 2)},
         "adjoint": {"form": "nufft" if nufft else "direct", "ms": round(k_ms["synth_adj"], 4),
                     "taps_ms": round(k_ms["nu_taps"], 4) if nufft else None,
                     "path_antenna_chirps_per_s": pac / (k_ms["synth_adj"] * 1e-3),
-                    # the tap kernel's row reads from LDS (7 float4 per (path, antenna,
-                    # chirp)) against the LDS bandwidth of the unit counts
-                    "taps_lds_read_gbs": round(LDS_READ_BYTES_PER_PAC * pac / (k_ms["nu_taps"] * 1e-3) / 1e9, 1)
+                    # the tap kernel's row reads from LDS (float4: 8 per (path, antenna,
+                    # node), 7 per (path, antenna, chirp) without nodes) against the LDS
+                    # bandwidth of the unit counts
+                    "doppler_nodes": q,
+                    "taps_lds_read_gbs": round(taps_bytes / (k_ms["nu_taps"] * 1e-3) / 1e9, 1) if nufft else None,
+                    "taps_lds_frac": round(taps_bytes / (k_ms["nu_taps"] * 1e-3) / 1e9 / PEAK_LDS_GBS, 4)
                     if nufft else None,
-                    "taps_lds_frac": round(LDS_READ_BYTES_PER_PAC * pac / (k_ms["nu_taps"] * 1e-3) / 1e9 /
-                                           PEAK_LDS_GBS, 4) if nufft else None,
                     "direct_sum_equivalent_tflops": round(FLOP_PER_PATH_SAMPLE["synth_adj"] * ps /
                                                           (k_ms["synth_adj"] * 1e-3) / 1e12, 2)},
         "trace": {"ray_bounces_per_s": queries / (k_ms["trace"] * 1e-3), "node_tests": node_tests,

@@ -202,8 +202,10 @@ size_t sbr_scratch_bytes(int32_t op, const sbr_mesh *mesh, const sbr_rays *rays,
 
 /* Build (mode 0) or refit (mode 1) the bounding volume hierarchy of a mesh.
  * BUILD sorts triangles by 30-bit Morton code of their centroids, forms the
- * binary radix tree (Karras, HPG 2012), computes boxes bottom-up and lays
- * nodes out in depth-first order with escape links for stackless traversal.
+ * binary radix tree (Karras, HPG 2012), computes each node's box as the union
+ * over its range of sorted leaves and lays nodes out in depth-first order with
+ * escape links for stackless traversal (16 bytes a node, the box in 16-bit
+ * steps of the mesh's bounds, rounded outwards).
  * REFIT keeps the tree of the last BUILD of this buffer (same faces, new
  * vertex positions) and recomputes boxes and triangle data.  A BUILD seals
  * the buffer with its face count; a REFIT of a buffer that no BUILD for
@@ -245,6 +247,12 @@ int sbr_trace(const sbr_mesh *mesh, const void *bvh, const sbr_radar *radar,
  * kernel's deconvolution follow.  The kernel's error is below 1e-6 of
  * sum_paths |I^s| per sample; each tap's rounding adds at most 2^-19 of that
  * largest component of its chunk.
+ * Where the ray grid's Doppler range is narrow against the chirps (more than four
+ * chirps per node), the chirps' phases are interpolated from q <= 32 Chebyshev
+ * nodes over that range (error below 1e-7 of sum_paths |I^s|): paths are spread
+ * into q rows per antenna instead of one per chirp, summed 32 at a time in single
+ * precision and then exactly at 2^-31 .. 2^-44 of the request's largest
+ * component, with the same independence of order.
  * With SBR_DIRECT_SUMS, or for other S, the sum is taken directly.
  * if_cube: device float [V][C][S][2], overwritten.  mats: host array of
  * n_mats (<= 64) entries, or NULL / 0 for all-conductor.  A hit id outside
@@ -375,8 +383,10 @@ typedef struct {
  * (Eq. 11).  For 16 <= S <= 1024 they are evaluated by a type-2 non-uniform
  * FFT (one 2S-point transform per row, shared by all paths, then 7 kernel taps
  * per path; exponential-of-semicircle kernel), whose error is below 1e-6 of
- * sum_s |weighted G_s| at every g; with SBR_DIRECT_SUMS, or for other S, by
- * direct summation.  Arguments as for sbr_synth_if; hits and flags must be
+ * sum_s |weighted G_s| at every g; with the Doppler nodes of sbr_synth_if (from
+ * two chirps per node on) the rows are combined over the chirps into q rows per
+ * antenna first, and a path takes 8 taps of each.  With SBR_DIRECT_SUMS, or for
+ * other S, they are evaluated by direct summation.  Arguments as for sbr_synth_if; hits and flags must be
  * those the forward used (plus SBR_ATTACHED, and SBR_PATHS_IN_SCRATCH when
  * the scratch still holds that forward's path records).  params: NULL,
  * or where to ADD the gradients of the material table (Eqs. 9-10 through
@@ -426,8 +436,9 @@ typedef struct {
 size_t sbr_batch_table_bytes(int32_t n_requests);
 
 /* sbr_synth_if for each of reqs[0..n) (host array), enqueued on `stream`:
- * every request's path stage, then ONE launch per sample-run length over the
- * synthesis blocks of all requests -- a device table (written by the call
+ * every request's path stage, then ONE launch per kernel and form (Doppler
+ * nodes, chirp rows, direct sums by sample-run length) over the synthesis blocks
+ * of all requests -- a device table (written by the call
  * into `table`, device memory of sbr_batch_table_bytes(n) bytes, not to be
  * reused until the stream has passed this call) gives each block its request
  * -- then each request's fixed-order reduction into its if_cube.  Every

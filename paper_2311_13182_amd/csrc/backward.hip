@@ -472,13 +472,15 @@ __host__ __device__ inline int node_stage(int S, int q, bool td) {
     return max(1, min(q, 61440 / (nu_row_len(S) * (td ? 24 : 16))));
 }
 
-// One work item of the node form: kNodePPL paths per lane; per antenna the
-// tap weights and the phase factor once, then per node the kNu8W taps (16-byte
-// LDS reads, 8 more for the taudot rows) times the node's Lagrange polynomial.
-// Bound by those LDS reads: 8 q (16 or 24) bytes per path and antenna.
+// One work item of the node form: a.tile paths from blk_p0 on, kNodePPL per lane
+// at a time; per antenna the tap weights and the phase factor once, then per
+// node the kNu8W taps (16-byte LDS reads, 8 more for the taudot rows) times the
+// node's Lagrange polynomial.  Bound by those LDS reads: 8 q (16 or 24) bytes
+// per path and antenna.  An item of one antenna whose rows are all in LDS keeps
+// them for all its paths.
 template <bool TD>
-__device__ __forceinline__ void adj_item_node(const AdjArgs &a, float4 *rsh, const int P, const int grp,
-                                              const int blk_p0) {
+__device__ __forceinline__ void adj_part_node(const AdjArgs &a, float4 *rsh, const int P, const int grp,
+                                              const int blk_p0, const bool have_rows) {
     constexpr int PPL = kNodePPL;
     const auto amp = gmem(a.rec.amp);
     const auto bet = gmem(a.rec.beta);
@@ -529,19 +531,21 @@ __device__ __forceinline__ void adj_item_node(const AdjArgs &a, float4 *rsh, con
         const auto rows_v = gmem4(a.nu_rows) + (size_t)v * Q * RL;
         for (int q0 = 0; q0 < Q; q0 += stage) {
             const int nr = min(stage, Q - q0);
-            __syncthreads();   // the previous stage has been read
-            for (int i = threadIdx.x; i < nr * RL; i += kNodeThreads) {
-                const F4 u = rows_v[(size_t)q0 * RL + i];
-                rsh[i] = make_float4(u.x, u.y, u.z, u.w);
-            }
-            if (TD) {
-                const auto t_v = gmem(a.td_rows) + ((size_t)v * Q + q0) * RL;
+            if (!have_rows) {   // uniform over the block
+                __syncthreads();   // the previous stage has been read
                 for (int i = threadIdx.x; i < nr * RL; i += kNodeThreads) {
-                    const F2 u = t_v[i];
-                    rs2[i] = make_float2(u.x, u.y);
+                    const F4 u = rows_v[(size_t)q0 * RL + i];
+                    rsh[i] = make_float4(u.x, u.y, u.z, u.w);
                 }
+                if (TD) {
+                    const auto t_v = gmem(a.td_rows) + ((size_t)v * Q + q0) * RL;
+                    for (int i = threadIdx.x; i < nr * RL; i += kNodeThreads) {
+                        const F2 u = t_v[i];
+                        rs2[i] = make_float2(u.x, u.y);
+                    }
+                }
+                __syncthreads();
             }
-            __syncthreads();
             for (int k = 0; k < nr; k++) {
                 const float2 nd = a.nd.node[q0 + k];
 #pragma unroll
@@ -597,6 +601,15 @@ __device__ __forceinline__ void adj_item_node(const AdjArgs &a, float4 *rsh, con
             gmem(a.abar_part)[(size_t)grp * a.rec.cap + pp[i]] = F2{abr[i], abi[i]};
             if (TD) gmem(a.tdb_part)[(size_t)grp * a.rec.cap + pp[i]] = tdb[i];
         }
+}
+
+template <bool TD>
+__device__ __forceinline__ void adj_item_node(const AdjArgs &a, float4 *rsh, const int P, const int grp,
+                                              const int blk_p0) {
+    const bool keep = a.v_per == 1 && node_stage(a.S, a.nd.q, TD) >= a.nd.q;
+    const int end = min(P, blk_p0 + a.tile);
+    for (int p0 = blk_p0; p0 < end; p0 += kNodeThreads * kNodePPL)
+        adj_part_node<TD>(a, rsh, P, grp, p0, keep && p0 > blk_p0);
 }
 
 // Path-stationary adjoint of Eq. (8).  For each (path, v, c) the sums
@@ -1552,6 +1565,16 @@ static void launch_geom(const GeomArgs &g, dim3 grid, hipStream_t s) {
     else hipLaunchKernelGGL((k_geom_adj<K, false>), grid, dim3(256), 0, s, g);
 }
 
+// Paths per work item of the node form: 1024, and up to eight times as many
+// while the path slots give 16384 items (a tenth of the slots may hold paths,
+// and about 512 blocks take the items).  An item's rows cost as much to load as
+// a few hundred of its paths: 2048^2 rays, 12 antennas, 16.8M slots 1.77 -> 1.44
+// ms (four times: 1.46), 1024^2 rays, 3.1M slots 97 -> 86 us (twice).
+static int node_tile(long long cap, int nvs) {
+    constexpr int part = kNodeThreads * kNodePPL;
+    return part * (int)std::max(1LL, std::min(8LL, cap * nvs / part / 16384));
+}
+
 int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream_t s) {
     if (n <= 0) return SBR_OK;
     // requests of the node form first, then those of the chirp-row form, then
@@ -1593,7 +1616,7 @@ int launch_backward_batch(const BackwardReq *reqs, int n, void *table, hipStream
         a.S = q.cd.S;
         a.v_per = bp.v_per;
         a.nvs = bp.nvs;
-        a.tile = node ? kNodeThreads * kNodePPL : nu ? 256 * kNuPPL : 256 * kAdjPPL;
+        a.tile = node ? node_tile(cap, bp.nvs) : nu ? 256 * kNuPPL : 256 * kAdjPPL;
         a.fcf = (float)q.cd.fc;
         a.sl_fs = (float)(q.cd.slope / q.cd.fs);
         a.tc = (float)q.cd.tc;
