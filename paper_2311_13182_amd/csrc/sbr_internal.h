@@ -177,6 +177,9 @@ constexpr int kPathBlock = 1024;   // rays per block of the counting kernel
 
 // Antennas (TX times RX) from which on a path's delays are written, and their
 // adjoints summed, by kernels of their own rather than by the path's lane.
+// Measured at 12 (path stage and geometry adjoint 1.32 ms together at 2048^2 rays,
+// with the summing kernel alone 0.45 ms more) and at 400 (0.65 ms, 0.16 with the
+// kernels); the line is drawn between them.
 constexpr int kSplitAntennas = 32;
 
 // Doppler nodes of the node form of the non-uniform FFT sums.  With nu =

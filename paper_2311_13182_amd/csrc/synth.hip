@@ -1026,7 +1026,7 @@ __global__ __launch_bounds__(256) void k_nu_synth_rows(const SynthArgs *__restri
 // polynomials L_j over them, row (v, c) of the cube is
 //   sum_j e^{2 pi j (c - cbar)(1 + s kappa) nu_j} F_j[v][s],
 //   F_j[v][s] = sum_p L_j(nu_p) A_p e^{2 pi j (alpha + cbar nu_p)} e^{2 pi j s g_p},  g_p = gamma + cbar eps,
-// so a path is spread into q rows of 2S points (q = 6 for the 2048^2-ray scene
+// so a path is spread into q rows of 2S points (q = 7 for the 2048^2-ray scene
 // at 1 m/s) instead of one row per chirp (128 there).
 // k_node_spread: block = (path chunk, antenna, group of cg nodes).  Real and
 // imaginary parts are separate 64-bit integer cells in LDS at 2^bits over the
